@@ -52,6 +52,12 @@ size_t ch_rhs_rows_lds_bytes(int state_dtype, int wr, int cpt, int nb);
 hipError_t launch_ch_rhs_rows(int state_dtype, int wr, int cpt, int nb, const RhsInst *rhs, const RowsInst *rows,
                               const RowGroup *work, int count, hipStream_t s);
 
+// The same for rows of a multiple of 4 elements (chquads.hip): one workgroup
+// per group of ch_quad_rows(nb) rows, 4 columns at a time per thread.
+int ch_quad_rows(int nb);
+hipError_t launch_ch_quads(int state_dtype, int nb, const RhsInst *rhs, const RowsInst *rows, const RowGroup *work,
+                           int count, hipStream_t s);
+
 // Mass: per-instance double sums of a state buffer.
 struct MassInst {
     const void *c;

@@ -109,19 +109,38 @@ struct CHPlan final : mxs_plan_s {
     bool fused = false, fused_ok = false;
     int fused_rows = 4, fused_cols = 1;
     DevBuf fused_work;
-    std::vector<RowRange> fused_ranges;
+    struct FusedRange {
+        int nb, first, count;
+        bool quads;   // the class is launched as launch_ch_quads
+    };
+    std::vector<FusedRange> fused_ranges;
     std::vector<int> class_order;   // instances ordered by register class of their rows
+    // The quad kernel takes a class whose rows are all a multiple of 4
+    // elements (whole quads, 16-byte aligned); the shapes of
+    // ch_rhs_rows_kernel take the others.  MXS_CH_FUSED_ROWS and
+    // MXS_CH_FUSED_COLS fix one of those shapes for every class (tests).
+    bool quads_off = false;
+    bool fused_shaped() const {   // some class has a workgroup shape to choose
+        for (const FusedRange &f : fused_ranges)
+            if (!f.quads) return true;
+        return false;
+    }
 
-    // Row groups of wr rows for the fused form, in class order.
+    // Row groups of the fused form in class order: wr rows, or as many as
+    // the quad kernel takes.
     hipError_t build_fused(int wr) {
         std::vector<RowGroup> work;
         fused_ranges.clear();
-        for (int g : class_order) {
-            const int nb = wave_nb(inst[g].nx);
-            if (fused_ranges.empty() || fused_ranges.back().nb != nb)
-                fused_ranges.push_back({nb, static_cast<int>(work.size()), 0});
-            for (int j0 = 0; j0 < inst[g].ny; j0 += wr) work.push_back({g, j0});
-            fused_ranges.back().count = static_cast<int>(work.size()) - fused_ranges.back().first;
+        for (size_t a = 0; a < class_order.size();) {
+            const int nb = wave_nb(inst[class_order[a]].nx);
+            size_t z = a;
+            bool quads = !quads_off;
+            for (; z < class_order.size() && wave_nb(inst[class_order[z]].nx) == nb; ++z)
+                quads = quads && inst[class_order[z]].nx % 4 == 0;
+            const int first = static_cast<int>(work.size()), step = quads ? ch_quad_rows(nb) : wr;
+            for (; a < z; ++a)
+                for (int j0 = 0; j0 < inst[class_order[a]].ny; j0 += step) work.push_back({class_order[a], j0});
+            fused_ranges.push_back({nb, first, static_cast<int>(work.size()) - first, quads});
         }
         fused_rows = wr;
         return fused_work.upload(work.data(), sizeof(RowGroup) * work.size());
@@ -188,10 +207,12 @@ struct CHPlan final : mxs_plan_s {
         if (fused) {
             hipError_t e = hipSuccess;
             const RowGroup *work = static_cast<const RowGroup *>(fused_work.ptr);
-            for (size_t q = 0; q < fused_ranges.size() && e == hipSuccess; ++q)
-                e = launch_ch_rhs_rows(dtype, fused_rows, fused_cols, fused_ranges[q].nb,
-                                       static_cast<const RhsInst *>(rhs_d[r].ptr), ri, work + fused_ranges[q].first,
-                                       fused_ranges[q].count, s);
+            const RhsInst *rh = static_cast<const RhsInst *>(rhs_d[r].ptr);
+            for (size_t q = 0; q < fused_ranges.size() && e == hipSuccess; ++q) {
+                const FusedRange &f = fused_ranges[q];
+                e = f.quads ? launch_ch_quads(dtype, f.nb, rh, ri, work + f.first, f.count, s)
+                            : launch_ch_rhs_rows(dtype, fused_rows, fused_cols, f.nb, rh, ri, work + f.first, f.count, s);
+            }
             if (e != hipSuccess) return e;
             return launch_cols(wdtype, dtype, 2, 1, static_cast<const ColsInst *>(cols_d[r].ptr),
                                map_of(colsAC_map), map_of(colsB_map), colsAC, colsB, bgroups, s);
@@ -441,6 +462,7 @@ struct CHPlan final : mxs_plan_s {
         if (fused_ok) {
             const int shapes[3][2] = {{4, 1}, {8, 1}, {4, 2}};
             for (const auto &sh : shapes) {
+                if (&sh != shapes && !fused_shaped()) break;
                 const size_t lds = ch_rhs_rows_lds_bytes(dtype, sh[0], sh[1], wave_nb(max_nx));
                 if (lds > 0 && lds <= static_cast<size_t>(device_lds_limit()))
                     cands.push_back({kRhsThreads, 16, row_nw, false, 1e30, true, sh[0], sh[1]});
@@ -642,6 +664,7 @@ struct CHPlan final : mxs_plan_s {
             const char *fcol = getenv("MXS_CH_FUSED_COLS");
             const bool r8 = fr && atoi(fr) == 8, c2 = fcol && atoi(fcol) == 2 && !r8;
             fused_cols = c2 ? 2 : 1;
+            quads_off = r8 || c2;
             hipError_t fe = build_fused(r8 ? 8 : 4);
             if (fe != hipSuccess) return hip_fail(fe, "row group table upload");
             fused_ok = true;

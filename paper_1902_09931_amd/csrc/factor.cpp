@@ -204,4 +204,30 @@ void fill_pow_table(const CyclicFactor &f, int bw, double *out) {
     }
 }
 
+// Entries as in StripTab (strips_dev.h).
+void fill_strip_tab(const CyclicFactor &f, int bw, int ny, int L, int spw, int nw, double *out) {
+    const ld p1 = f.p1, p2 = bw == 2 ? f.p2 : 0;
+    const M2 M{p1, p2, 1, 0};
+    const int nseg = (ny + L - 1) / L, wlast = (nseg - 1) / spw;
+    const int last = ny - (nseg - 1) * L;
+    const M2 T = mpow(M, L);
+    M2 r{1, 0, 0, 1};
+    for (int k = 0; k <= spw; ++k, r = mul(r, T)) store(r, out + 4 * k);
+    double *fw = out + 4 * (spw + 1), *bwd = fw + 4 * nw;
+    for (int w = 0; w < nw; ++w) {
+        const long long first = static_cast<long long>(w) * spw * L;
+        store(mpow(M, w <= wlast ? first : 0), fw + 4 * w);
+        // from the column's end to the end of wavefront w's segments, or, in
+        // the last wavefront, over the last segment
+        store(mpow(M, w < wlast ? ny - first - static_cast<long long>(spw) * L : last), bwd + 4 * w);
+    }
+    double *tl = bwd + 4 * nw;
+    store(mpow(M, last), tl);
+    store(mpow(M, ny - static_cast<long long>(wlast) * spw * L), tl + 4);
+    const M2 Mn = mpow(M, ny);
+    const ld a = 1 - Mn.a, b = -Mn.b, c = -Mn.c, d = 1 - Mn.d;
+    const ld det = a * d - b * c;
+    store(M2{d / det, -b / det, -c / det, a / det}, tl + 8);
+}
+
 }  // namespace mxs

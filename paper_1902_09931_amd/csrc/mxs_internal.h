@@ -14,6 +14,10 @@ namespace mxs {
 // global loads and stores, or scalar loads where uniform.
 template <typename T> using gptr = T __attribute__((address_space(1))) *;
 template <typename T> __device__ __forceinline__ gptr<T> as_global(T *p) { return (gptr<T>)p; }
+// Tables that no kernel writes, read through the constant address space:
+// loads at uniform addresses are scalar loads wherever they stand.
+template <typename T> using cptr = const T __attribute__((address_space(4))) *;
+template <typename T> __device__ __forceinline__ cptr<T> as_constant(const T *p) { return (cptr<T>)p; }
 
 // ---------------------------------------------------------------------------
 // Storage types.  bfloat16 is carried as its 16 raw bits.

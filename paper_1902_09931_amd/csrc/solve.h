@@ -115,8 +115,27 @@ struct ColsInst {
     double Cinv[4];             // (I - M^n)^-1
 };
 
+// Columns held in registers: a workgroup solves a strip of columns in one
+// launch (strips_dev.h).
+struct StripInst {
+    const void *rhs;            // rhs dtype
+    void *x;                    // output dtype
+    const void *cur;            // CH update: C^n (output dtype), or nullptr
+    const void *prev;           // CH update: C^{n-1} (output dtype), or nullptr
+    const double *tab;          // strip power table
+    long long ld;
+    int nx, ny;
+    int L, nseg;                // rows per segment and segments per column
+    int blk0;                   // first workgroup of this instance
+    double p1, p2, invK;
+};
+
 // Fill the column coefficients of an instance with n = ny rows.
 void fill_cols_coef(const CyclicFactor &f, int bw, int ny, ColsInst *ci);
+// Fill the strip power table of a column of ny rows in segments of L rows,
+// spw segments per wavefront, nw wavefronts (strip_tab_doubles values).
+inline size_t strip_tab_doubles(int spw, int nw) { return 4 * (static_cast<size_t>(spw) + 1 + 2 * nw + 3); }
+void fill_strip_tab(const CyclicFactor &f, int bw, int ny, int L, int spw, int nw, double *out);
 
 hipError_t launch_ragged_lines(int dtype, int bw, const RaggedLines &a, int nw, int grid,
                                size_t lds, hipStream_t s);

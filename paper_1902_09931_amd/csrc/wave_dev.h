@@ -18,6 +18,7 @@ struct Mat {
 };
 
 __device__ __forceinline__ Mat load_mat(gptr<const double> m) { return Mat{m[0], m[1], m[2], m[3]}; }
+__device__ __forceinline__ Mat load_mat(cptr<double> m) { return Mat{m[0], m[1], m[2], m[3]}; }
 
 // s' = M s + (r, 0); the p2 term does not depend on the newest value, so the
 // dependent chain is one FMA long.
@@ -42,7 +43,7 @@ __device__ __forceinline__ Mat mat_mul(const Mat &x, const Mat &y) {
 }
 
 // M^k for 0 <= k <= 16 * 256, from the table (pw: M^k, k <= 256; pb: M^(256 c))
-__device__ __forceinline__ Mat pow_mat(gptr<const double> pw, gptr<const double> pb, int k) {
+template <class P> __device__ __forceinline__ Mat pow_mat(P pw, P pb, int k) {
     return mat_mul(load_mat(pw + 4 * (k & (kWaveBlock - 1))), load_mat(pb + 4 * (k / kWaveBlock)));
 }
 

@@ -109,6 +109,12 @@ struct CHPlan final : mxs_plan_s {
     bool fused = false, fused_ok = false;
     int fused_rows = 4, fused_cols = 1;
     DevBuf fused_work;
+    // fused form: the columns as strips (one launch) where strip_shape >= 0,
+    // else the three phases.  Grids of at most 64 rows keep the phases: they
+    // are two segments per column, and the flat grids that have them are
+    // bound by their long rows.
+    int strips = -1, strip_blocks = 0;
+    DevBuf strip_d[3], strip_map, strip_tabs;
     struct FusedRange {
         int nb, first, count;
         bool quads;   // the class is launched as launch_ch_quads
@@ -214,6 +220,9 @@ struct CHPlan final : mxs_plan_s {
                             : launch_ch_rhs_rows(dtype, fused_rows, fused_cols, f.nb, rh, ri, work + f.first, f.count, s);
             }
             if (e != hipSuccess) return e;
+            if (strips >= 0)
+                return launch_strips(wdtype, dtype, 2, 1, strips, static_cast<const StripInst *>(strip_d[r].ptr),
+                                     map_of(strip_map), strip_blocks, s);
             return launch_cols(wdtype, dtype, 2, 1, static_cast<const ColsInst *>(cols_d[r].ptr),
                                map_of(colsAC_map), map_of(colsB_map), colsAC, colsB, bgroups, s);
         }
@@ -544,7 +553,7 @@ struct CHPlan final : mxs_plan_s {
 
     void info(char *buf, int len) const override {
         const int launches = persistent ? 1
-                             : fused  ? static_cast<int>(fused_ranges.size()) + 3
+                             : fused  ? static_cast<int>(fused_ranges.size()) + (strips >= 0 ? 1 : 3)
                                       : 1 + (row_ranges.empty() ? 1 : static_cast<int>(row_ranges.size())) + 3;
         int n = snprintf(buf, len, "ch instances=%d dtype=%d step=%s launches_per_step=%d rhs_rows=%d rhs_threads=%d "
                          "rhs_blocks=%d cols_blocks=%d colsB_groups=%d",
@@ -558,6 +567,7 @@ struct CHPlan final : mxs_plan_s {
         if (best_persist && n < len)
             n += snprintf(buf + n, len - n, " tuned_us_persistent=%.1f", best_persist_t * 1e6);
         if (fused && n < len) n += snprintf(buf + n, len - n, " fused_rows=%d fused_cols=%d", fused_rows, fused_cols);
+        if (fused && strips >= 0 && n < len) n += snprintf(buf + n, len - n, " columns=strips shape=%d", strips);
         if (best_fused_t < 1e29 && n < len)
             n += snprintf(buf + n, len - n, " tuned_us_fused=%.1f", best_fused_t * 1e6);
         if (row_ranges.empty() && n < len)
@@ -587,6 +597,22 @@ struct CHPlan final : mxs_plan_s {
             bgroups = cols_b_groups(static_cast<int>(segs / n));
         }
         const int bcols = cols_b_cols(bgroups);
+        int max_ny = 0;
+        long long sum_nx = 0;
+        for (const Inst &I : inst) {
+            max_ny = std::max(max_ny, I.ny);
+            sum_nx += I.nx;
+        }
+        strips = reg_rows && max_ny > 2 * kSeg ? strip_shape_for(max_ny, sum_nx, 1) : -1;
+        const size_t stab = strips >= 0 ? strip_tab_size(strips) : 0;
+        std::vector<double> st(stab * n);
+        std::vector<StripInst> strip_h(strips >= 0 ? n : 0);
+        std::vector<int> strip_units(n);
+        if (strips >= 0) {
+            hipError_t e = strip_tabs.alloc(sizeof(double) * st.size());
+            if (e != hipSuccess) return hip_fail(e, "strip table allocation");
+        }
+        strip_blocks = 0;
         for (int g = 0; g < n; ++g) {
             Inst &I = inst[g];
             const double a = 2.0 / 3.0 * D * gamma * I.dt;
@@ -608,6 +634,18 @@ struct CHPlan final : mxs_plan_s {
             rows_h[g] = ro;
             fill_pow_table(fx, 2, pt.data() + static_cast<size_t>(4) * kPowEntries * g);
 
+            if (strips >= 0) {
+                StripInst &si = strip_h[g];
+                si = StripInst{};
+                fill_strip(fy, 2, I.nx, I.ny, strips, &si, st.data() + stab * g);
+                si.tab = static_cast<const double *>(strip_tabs.ptr) + stab * g;
+                si.ld = I.nx;
+                si.rhs = I.w.ptr;
+                si.blk0 = strip_blocks;
+                const int w = strip_shape(strips).columns;
+                strip_units[g] = (I.nx + w - 1) / w;
+                strip_blocks += strip_units[g];
+            }
             ColsInst co{};
             fill_cols_coef(fy, 2, I.ny, &co);
             co.ld = I.nx;
@@ -629,6 +667,20 @@ struct CHPlan final : mxs_plan_s {
                 cc.x = I.buf[(r + 2) % 3];
                 cols_h[r][g] = cc;
             }
+        }
+        if (strips >= 0) {
+            // (the instances hold addresses inside the table's allocation)
+            hipError_t se = hipMemcpy(strip_tabs.ptr, st.data(), sizeof(double) * st.size(), hipMemcpyHostToDevice);
+            for (int r = 0; r < 3 && se == hipSuccess; ++r) {
+                for (int g = 0; g < n; ++g) {
+                    strip_h[g].prev = inst[g].buf[r % 3];
+                    strip_h[g].cur = inst[g].buf[(r + 1) % 3];
+                    strip_h[g].x = inst[g].buf[(r + 2) % 3];
+                }
+                se = strip_d[r].upload(strip_h.data(), sizeof(StripInst) * n);
+            }
+            if (se == hipSuccess && n > 1) se = upload_map(strip_map, strip_units);
+            if (se != hipSuccess) return hip_fail(se, "strip tables upload");
         }
         // global line numbers: instances grouped by register class, so that
         // every class is one contiguous range of lines

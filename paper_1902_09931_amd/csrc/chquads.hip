@@ -171,8 +171,6 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
                 hal[32 + lane] = hcv * hcv * hcv - hcv;
             }
             wave_sync();
-            const int side = lane == 0 ? 0 : 2;   // lane 0 needs the left pair, the last lane the right one
-
             A fx[ORDERED ? GIN : 1][6], dv[ORDERED ? GIN : 1][4];
 #pragma unroll
             for (int u = 0; u < GIN; ++u) {
@@ -189,22 +187,24 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) f[1 + i] = A(0);
                 if (u >= 1 && u < GIN - 1) {
-                    const A h0 = hal[4 * u + side], h1 = hal[4 * u + side + 1];
-                    x[1] = lane_shift<kPrevLane>(x[5], h1);
-                    const A r1 = lane_shift<kNextLane>(x[2], h0);
-                    x[6] = lane == lv ? h0 : r1;
+                    A hb[4];   // the row's halo: two columns before lane 0, two after lane lv
+                    lds4(hal + 4 * u, hb);
+                    x[1] = lane_shift<kPrevLane>(x[5], hb[1]);
+                    const A r1 = lane_shift<kNextLane>(x[2], hb[2]);
+                    x[6] = lane == lv ? hb[2] : r1;
                     if (u >= 2 && u < GIN - 2) {
-                        x[0] = lane_shift<kPrevLane>(x[4], h0);
-                        const A r2 = lane_shift<kNextLane>(x[3], h1);
-                        x[7] = lane == lv ? h1 : r2;
+                        x[0] = lane_shift<kPrevLane>(x[4], hb[0]);
+                        const A r2 = lane_shift<kNextLane>(x[3], hb[3]);
+                        x[7] = lane == lv ? hb[3] : r2;
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) f[1 + i] = c[u][i] * c[u][i] * c[u][i] - c[u][i];
                     if (u >= 2 && u < GIN - 2) {
-                        const A g0 = hal[32 + 4 * u + side], g1 = hal[32 + 4 * u + side + 1];
-                        f[0] = lane_shift<kPrevLane>(f[4], g1);
-                        const A rf = lane_shift<kNextLane>(f[1], g0);
-                        f[5] = lane == lv ? g0 : rf;
+                        A hf[4];
+                        lds4(hal + 32 + 4 * u, hf);
+                        f[0] = lane_shift<kPrevLane>(f[4], hf[1]);
+                        const A rf = lane_shift<kNextLane>(f[1], hf[2]);
+                        f[5] = lane == lv ? hf[2] : rf;
                     }
                 }
                 if constexpr (ORDERED) {

@@ -137,6 +137,24 @@ void fill_cols_coef(const CyclicFactor &f, int bw, int ny, ColsInst *ci);
 inline size_t strip_tab_doubles(int spw, int nw) { return 4 * (static_cast<size_t>(spw) + 1 + 2 * nw + 3); }
 void fill_strip_tab(const CyclicFactor &f, int bw, int ny, int L, int spw, int nw, double *out);
 
+// Strip shapes: threads per workgroup, columns per strip, most rows per
+// thread; a shape solves columns of at most threads / columns * rows rows.
+struct StripShape {
+    int threads, columns, rows;
+};
+// The shape for columns of at most ny_max rows, sum_nx columns in all, or -1
+// where the three phases are the better choice (epilogue as in launch_cols).
+int strip_shape_for(int ny_max, long long sum_nx, int epilogue);
+StripShape strip_shape(int shape);
+size_t strip_tab_size(int shape);   // doubles in the power table of one instance
+// Fill the coefficients of an instance (not its pointers, pitch, table
+// address and first workgroup) and its power table.
+void fill_strip(const CyclicFactor &f, int bw, int nx, int ny, int shape, StripInst *si, double *tab);
+// One launch over every strip; map[b] is the instance of workgroup b
+// (nullptr: all belong to instance 0).
+hipError_t launch_strips(int rhs_dtype, int x_dtype, int bw, int epilogue, int shape, const StripInst *inst,
+                         const int *map, int blocks, hipStream_t s);
+
 hipError_t launch_ragged_lines(int dtype, int bw, const RaggedLines &a, int nw, int grid,
                                size_t lds, hipStream_t s);
 // map[li] (map[b]) is the instance of line li (workgroup b); nullptr: all

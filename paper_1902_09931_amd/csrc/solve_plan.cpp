@@ -40,6 +40,8 @@ struct SolvePlan final : mxs_plan_s {
     // captured into a graph) and swap() only flips cur
     RowsInst rows{};
     ColsInst cols{};
+    StripInst strip{};
+    int shape = -1;   // columns: strip shape, or -1 for the three phases
     DevBuf tables[2], carry, pow;
     int cur = 0;
     // register kernel classes (blocks per line, first line, line count), for
@@ -68,6 +70,11 @@ struct SolvePlan final : mxs_plan_s {
                 ri.in = in;
                 ri.out = out;
                 e = tables[k].upload(&ri, sizeof ri);
+            } else if (shape >= 0) {
+                StripInst si = strip;
+                si.rhs = in;
+                si.x = out;
+                e = tables[k].upload(&si, sizeof si);
             } else {
                 ColsInst ci = cols;
                 ci.rhs = in;
@@ -113,6 +120,9 @@ struct SolvePlan final : mxs_plan_s {
                 e = launch_wave_rows(dtype, bw, wave[0].nb, ti, nullptr, 0, nlines, s);
             else
                 e = launch_rows(dtype, bw, ti, nullptr, nlines, nw, grid, lds, s);
+        } else if (shape >= 0) {
+            e = launch_strips(dtype, dtype, bw, 0, shape, static_cast<const StripInst *>(tables[cur].ptr), nullptr,
+                              blocksAC, s);
         } else {
             e = launch_cols(dtype, dtype, bw, 0, static_cast<const ColsInst *>(tables[cur].ptr), nullptr,
                             nullptr, blocksAC, blocksB, bgroups, s);
@@ -195,6 +205,9 @@ struct SolvePlan final : mxs_plan_s {
     }
     void info(char *buf, int len) const override {
         int n = snprintf(buf, len, "cyclic_solve geometry=%d bw=%d dtype=%d", geometry, bw, dtype);
+        if (geometry == MXS_LINES_COLS && n < len)
+            n += shape >= 0 ? snprintf(buf + n, len - n, " columns=strips shape=%d launches=1", shape)
+                            : snprintf(buf + n, len - n, " columns=phases launches=3");
         const bool lds_kernel = geometry == MXS_LINES_RAGGED ? nlong > 0 : wave.empty();
         if (geometry != MXS_LINES_COLS && lds_kernel && n < len)
             n += snprintf(buf + n, len - n, " lds_kernel_lines=%d waves_per_line=%d grid=%d lds=%zu",
@@ -357,6 +370,14 @@ extern "C" mxs_status mxs_create_cyclic_solve(int bw, const double *coef, int ge
             p->nmax = nx;
             if (nx <= kWaveLineMax && !force_lds_lines()) p->wave.push_back({wave_nb(nx), 0, ny});
             p->set_waves(line_waves(nx));
+        } else if ((p->shape = strip_shape_for(ny, nx, 0)) >= 0) {
+            std::vector<double> tab(strip_tab_size(p->shape));
+            fill_strip(p->f, bw, nx, ny, p->shape, &p->strip, tab.data());
+            p->strip.ld = ld;
+            const int w = strip_shape(p->shape).columns;
+            p->blocksAC = (nx + w - 1) / w;
+            e = p->pow.upload(tab.data(), sizeof(double) * tab.size());
+            p->strip.tab = static_cast<const double *>(p->pow.ptr);
         } else {
             fill_cols_coef(p->f, bw, ny, &p->cols);
             p->cols.ld = ld;

@@ -56,7 +56,7 @@ __device__ __forceinline__ void strip_block(const StripInst &I, const int strip,
     const bool valid = col < I.nx;
     const long long ld = I.ld;
     const double p1 = I.p1, p2 = I.p2;
-    const gptr<const double> tab = as_global(I.tab);
+    const cptr<double> tab = as_constant(I.tab);
     const long long base = valid ? col : I.nx - 1;
 
     // the segment's rows (rows past the end repeat the last one; their values are not used)

@@ -58,7 +58,8 @@ int ch_quad_rows(int nb);
 hipError_t launch_ch_quads(int state_dtype, int nb, const RhsInst *rhs, const RowsInst *rows, const RowGroup *work,
                            int count, hipStream_t s);
 
-// Mass: per-instance double sums of a state buffer.
+// Mass: per-instance double sums of a state buffer, written to out (pinned
+// host memory); err, if not null, is copied to err_out (pinned) beside them.
 struct MassInst {
     const void *c;
     long long n;
@@ -66,6 +67,7 @@ struct MassInst {
 };
 constexpr int kMassThreads = 256;
 hipError_t launch_ch_mass(int state_dtype, const MassInst *inst, const int *map, int ninst,
-                          int blocks, double *partial, double *out, hipStream_t s);
+                          int blocks, double *partial, double *out, const unsigned *err, unsigned *err_out,
+                          hipStream_t s);
 
 }  // namespace mxs

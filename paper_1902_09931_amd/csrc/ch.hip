@@ -57,19 +57,33 @@ __global__ void __launch_bounds__(kMassThreads) mass_partial_kernel(const MassIn
     const long long b = min(I.n, a + chunk);
     const gptr<const T> c = as_global(static_cast<const T *>(I.c));
     double s = 0.0;
-    for (long long i = a + threadIdx.x; i < b; i += kMassThreads) s += elem_f64<T>(c, i);
+    // 8 loads in flight per thread; the sum keeps one fixed order
+    constexpr int U = 8;
+    long long i = a + threadIdx.x;
+    for (; i + (U - 1) * kMassThreads < b; i += U * kMassThreads) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = elem_f64<T>(c, i + u * kMassThreads);
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+    }
+    for (; i < b; i += kMassThreads) s += elem_f64<T>(c, i);
     const double tot = block_sum(s, red);
     if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
+// out and err_out are pinned host memory: the results need no copy after the
+// kernel.  err: the persistent step's error word, or nullptr.
 __global__ void __launch_bounds__(kMassThreads) mass_final_kernel(const MassInst *__restrict__ inst,
-                                                                 const double *partial, double *out) {
+                                                                 const double *partial, double *out,
+                                                                 const unsigned *err, unsigned *err_out) {
     __shared__ double red[kMassThreads];
+    if (err && blockIdx.x == 0 && threadIdx.x == 0) *as_global(err_out) = *as_global(err);
     const MassInst &I = inst[blockIdx.x];
     double s = 0.0;
     for (int i = threadIdx.x; i < I.nblk; i += kMassThreads) s += partial[I.blk0 + i];
     const double tot = block_sum(s, red);
-    if (threadIdx.x == 0) out[blockIdx.x] = tot;
+    if (threadIdx.x == 0) as_global(out)[blockIdx.x] = tot;
 }
 
 template <typename T, typename TW>
@@ -82,10 +96,11 @@ hipError_t rhs_one(const RhsInst *inst, const int *map, int blocks, int threads,
 
 template <typename T>
 hipError_t mass_one(const MassInst *inst, const int *map, int ninst, int blocks, double *partial,
-                    double *out, hipStream_t s) {
+                    double *out, const unsigned *err, unsigned *err_out, hipStream_t s) {
     hipLaunchKernelGGL((mass_partial_kernel<T>), dim3(blocks), dim3(kMassThreads), 0, s, inst, map,
                        partial);
-    hipLaunchKernelGGL(mass_final_kernel, dim3(ninst), dim3(kMassThreads), 0, s, inst, partial, out);
+    hipLaunchKernelGGL(mass_final_kernel, dim3(ninst), dim3(kMassThreads), 0, s, inst, partial, out, err,
+                       err_out);
     return hipGetLastError();
 }
 
@@ -102,11 +117,12 @@ hipError_t launch_ch_rhs(int state_dtype, const RhsInst *inst, const int *map, i
 }
 
 hipError_t launch_ch_mass(int state_dtype, const MassInst *inst, const int *map, int ninst,
-                          int blocks, double *partial, double *out, hipStream_t s) {
+                          int blocks, double *partial, double *out, const unsigned *err, unsigned *err_out,
+                          hipStream_t s) {
     switch (state_dtype) {
-    case F64: return mass_one<double>(inst, map, ninst, blocks, partial, out, s);
-    case F32: return mass_one<float>(inst, map, ninst, blocks, partial, out, s);
-    case BF16: return mass_one<bf16>(inst, map, ninst, blocks, partial, out, s);
+    case F64: return mass_one<double>(inst, map, ninst, blocks, partial, out, err, err_out, s);
+    case F32: return mass_one<float>(inst, map, ninst, blocks, partial, out, err, err_out, s);
+    case BF16: return mass_one<bf16>(inst, map, ninst, blocks, partial, out, err, err_out, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -87,8 +87,8 @@ struct CHPlan final : mxs_plan_s {
         int nb, first, count;
     };
     std::vector<RowRange> row_ranges;
-    DevBuf partial, mass_out;
-    double *mass_host = nullptr;
+    DevBuf partial;
+    double *mass_host = nullptr;   // pinned: a mass per instance, then the 3 sums of the diagnostics
     int bgroups = 16;   // phase B threads per column
     int rhs_blocks = 0, rhs_rows = 16, rhs_threads = kRhsThreads, row_lines = 0, row_grid = 1, row_nw = 1, colsAC = 0, colsB = 0,
         mass_blocks = 0, max_nx = 0;
@@ -287,15 +287,9 @@ struct CHPlan final : mxs_plan_s {
 
     mxs_status mass(double *out, hipStream_t s) {
         const int r = static_cast<int>(steps % 3);
-        hipError_t e = launch_ch_mass(dtype, static_cast<const MassInst *>(mass_d[r].ptr),
-                                      map_of(mass_map), ninst(), mass_blocks, static_cast<double *>(partial.ptr),
-                                      static_cast<double *>(mass_out.ptr), s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(mass_host, mass_out.ptr, sizeof(double) * ninst(),
-                               hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess && bar.ptr)
-            e = hipMemcpyAsync(flag_host, static_cast<unsigned *>(bar.ptr) + 3, sizeof(unsigned),
-                               hipMemcpyDeviceToHost, s);
+        unsigned *word = bar.ptr ? static_cast<unsigned *>(bar.ptr) + 3 : nullptr;
+        hipError_t e = launch_ch_mass(dtype, static_cast<const MassInst *>(mass_d[r].ptr), map_of(mass_map), ninst(),
+                                      mass_blocks, static_cast<double *>(partial.ptr), mass_host, word, flag_host, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(e, "mass reduction");
         if (bar.ptr && *flag_host) {
@@ -316,7 +310,7 @@ struct CHPlan final : mxs_plan_s {
     // scratch is allocated on the first call and kept by the plan, or, with
     // noalloc, taken from the library's static per-device scratch (nothing
     // allocated; grids up to kNoAllocDiagPoints points).
-    DevBuf diag_spec, diag_partial, diag_out;
+    DevBuf diag_spec, diag_partial;
     mxs_status coarsening(int k, double *s_out, double *k1_out, hipStream_t s, bool noalloc) {
         const Inst &I = inst[k];
         if (!diag_shape_ok(I.nx, I.ny))
@@ -336,20 +330,17 @@ struct CHPlan final : mxs_plan_s {
             const size_t part = sizeof(double) * (static_cast<size_t>(I.ny) + 2 * I.nx);
             if (diag_spec.bytes < spec) e = diag_spec.alloc(spec);
             if (e == hipSuccess && diag_partial.bytes < part) e = diag_partial.alloc(part);
-            if (e == hipSuccess && !diag_out.ptr) e = diag_out.alloc(3 * sizeof(double));
             if (e != hipSuccess) return hip_fail(e, "diagnostics scratch allocation");
             d.spec = static_cast<double2 *>(diag_spec.ptr);
             d.partial = static_cast<double *>(diag_partial.ptr);
-            d.out = static_cast<double *>(diag_out.ptr);
         }
         d.c = I.buf[(steps % 3 + 1) % 3];
         d.nx = I.nx;
         d.ny = I.ny;
         d.kx0 = 2.0 * M_PI / (I.nx * I.dx);
         d.ky0 = 2.0 * M_PI / (I.ny * I.dy);
-        double h[3];
+        const double *h = d.out = mass_host + ninst();
         e = launch_coarsening(dtype, d, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(h, d.out, sizeof h, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(e, "coarsening diagnostics");
         const double mean_c2 = h[0] / (static_cast<double>(I.nx) * I.ny);
@@ -733,7 +724,8 @@ struct CHPlan final : mxs_plan_s {
         for (int r = 0; r < 3; ++r) mass_h[r].resize(n);
         for (int g = 0; g < n; ++g) {
             const long long npts = static_cast<long long>(inst[g].nx) * inst[g].ny;
-            const int nblk = static_cast<int>(std::min<long long>(256, (npts + 65535) / 65536));
+            // 4096 points per workgroup (16 per thread), at most 1024 workgroups
+            const int nblk = static_cast<int>(std::min<long long>(1024, (npts + 4095) / 4096));
             for (int r = 0; r < 3; ++r) {
                 MassInst m{};
                 m.c = inst[g].buf[(r + 1) % 3];
@@ -768,8 +760,7 @@ struct CHPlan final : mxs_plan_s {
             if (e == hipSuccess) e = upload_map(mass_map, mbk);
         }
         if (e == hipSuccess) e = partial.alloc(sizeof(double) * mass_blocks);
-        if (e == hipSuccess) e = mass_out.alloc(sizeof(double) * n);
-        if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&mass_host), sizeof(double) * n, 0);
+        if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&mass_host), sizeof(double) * (n + 3), 0);
         if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&flag_host), sizeof(unsigned), 0);
         if (e != hipSuccess) return hip_fail(e, "plan tables upload");
         *flag_host = 0;

@@ -259,8 +259,9 @@ mxs_status mxs_ch_ensemble_create(int count, const int *nx, const int *ny,
                                   void *const *c_cur, void *const *c_next,
                                   mxs_plan *plan);
 
-/* Enqueue nsteps steps on a stream.  With use_graph != 0 each step replays
- * a captured HIP graph (one per rotation of the three buffers). */
+/* Enqueue nsteps steps on a stream.  use_graph != 0 lets a step replay a
+ * captured HIP graph (one per rotation of the three buffers) in the forms
+ * where that is not slower than launching its kernels: the persistent one. */
 mxs_status mxs_ch_step(mxs_plan plan, int nsteps, int use_graph, void *hip_stream);
 
 /* How a step is launched.  MXS_CH_SEPARATE: one launch per kernel of the
@@ -273,8 +274,9 @@ mxs_status mxs_ch_step(mxs_plan plan, int nsteps, int use_graph, void *hip_strea
  * launch end early, and the next mxs_ch_mass returns MXS_ERR_HIP.
  * MXS_CH_FUSED: the right-hand side of the x sweep is formed inside the row
  * solves, so that it never goes to memory (one launch per register class of
- * rows, then the three column phases; rows of at most 4096 elements, else
- * MXS_ERR_UNSUPPORTED).  The three give the same step up to the order of
+ * rows, then the column solves: one launch for grids of 65 to 2048 rows
+ * whose columns fit a workgroup's registers, else three phases; rows of at
+ * most 4096 elements, else MXS_ERR_UNSUPPORTED).  The three give the same step up to the order of
  * rounding.  Plans start in MXS_CH_SEPARATE; mxs_autotune times every mode
  * the plan supports and keeps the fastest.  With use_graph the persistent
  * launch is captured in the step's graph. */

@@ -35,7 +35,8 @@ HBM_PEAK_GBS = 8000.0
 # (FETCH_SIZE, WRITE_SIZE), valid while the kernel sources and the tile
 # layout are the ones it was taken with.
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "stencil2d_8192_f64_traffic.json")
-TRAFFIC_SOURCES = ["paper_1902_09931_amd/csrc/stencil2d.hip", "paper_1902_09931_amd/csrc/mxs_internal.h"]
+TRAFFIC_SOURCES = ["paper_1902_09931_amd/csrc/stencil2d.hip", "paper_1902_09931_amd/csrc/stencil2d_dev.h",
+                   "paper_1902_09931_amd/csrc/stencil2d_block_dev.h", "paper_1902_09931_amd/csrc/mxs_internal.h"]
 # tile layouts (rows, order, threads, streaming stores) used by the counter runs
 # Counter-run layouts per stencil kind (alternatives after "|"): the
 # autotuner's choices for the 8192^2 FP64 set; the 3x3 kernels have been

@@ -117,11 +117,6 @@ namespace {
 
 int vec_elems(int dtype) { return dtype == F64 ? St<double>::V : dtype == F32 ? St<float>::V : St<bf16>::V; }
 
-bool vec_aligned(const void *p, int dtype) {
-    const uintptr_t bytes = static_cast<uintptr_t>(vec_elems(dtype)) * dtype_size(dtype);
-    return reinterpret_cast<uintptr_t>(p) % bytes == 0;
-}
-
 // Padded weights NWY x NWX in the accumulation type, followed by the same
 // window flipped vertically (row q holds window row T + B - q): the kernel
 // reads the second copy for row chunks it walks upward.
@@ -172,23 +167,50 @@ struct Stencil2DPlan final : mxs_plan_s {
         a.nchunks = (a.ny + rows - 1) / rows;
     }
 
-    // Layout before tuning: streaming stores; row chunks sized per direction
-    // (short for x, tall for y, medium for xy), shrunk until the grid keeps
-    // several workgroups per CU.
+    // Widest workgroup whose strip fits in a row, at most `most` threads (64
+    // where no strip fits: the strip then goes element by element).
+    int fit_threads(int most) const {
+        while (most > 64 && most * vec_elems(dtype) > a.nx) most /= 2;
+        return most;
+    }
+
+    // Layout before tuning, from the layouts that tuning picks (times of the
+    // streaming form with 256 threads against the one taken here).  Windows
+    // over 3 or 5 rows: block form of 8 input rows (2000^2 FP64 3x3 with a
+    // point function 22.4 / 15.8 us, 3000^2 FP32 5x5 32.4 / 21.1); 9 rows in
+    // double and float: block form of 16 (3001 x 2003 FP32 17.6 / 12.0).
+    // bfloat16: x neighbours by lanes, whose 8 values per thread and row would
+    // fill the LDS rows with floats (8192^2 5 taps along x 76 / 59, 3x3 105 /
+    // 72); its 5-column windows over several rows would not fit the registers
+    // of a block and stream.  Everything else streams.
     void default_layout() {
-        int rows = nwy == 1 ? 4 : (nwx == 1 ? 64 : 16);
-        const int W = 256 * vec_elems(dtype);
-        const long long strips = (a.nx + W - 1) / W;
-        const long long want = 8LL * device_cu_count();
-        while (rows > std::max(4, nwy) && strips * ((a.ny + rows - 1) / rows) < want) rows /= 2;
-        set_layout(rows, 1, 256, 1);
+        const bool xs4 = stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, 4);
+        const bool xs8 = stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, 8);
+        if (nwy == 1 && dtype == BF16 && xs4) {
+            set_layout(4, 1, fit_threads(256), 1, 4, 1);
+        } else if (nwy > 1 && dtype == BF16 && nwx == 3 && xs8) {
+            set_layout(8, 2, fit_threads(128), 1, 8, 1);
+        } else if (nwx == 1 && stencil2d_block_ok(dtype, nwx, nwy, nwy == 9 ? 16 : 8)) {
+            set_layout(8, 1, fit_threads(nwy == 9 ? 256 : 128), 1, nwy == 9 ? 16 : 8);
+        } else if (dtype != BF16 && stencil2d_block_ok(dtype, nwx, nwy, 8)) {
+            set_layout(8, 2, fit_threads(128), 1, 8);
+        } else {
+            // row chunks sized per direction (short for x, tall for y, medium
+            // for xy), shrunk until the grid keeps several workgroups per CU
+            int rows = nwy == 1 ? 4 : (nwx == 1 ? 64 : 16);
+            const int W = 256 * vec_elems(dtype);
+            const long long strips = (a.nx + W - 1) / W;
+            const long long want = (nwy >= 9 ? 2LL : 8LL) * device_cu_count();
+            while (rows > std::max(4, nwy) && strips * ((a.ny + rows - 1) / rows) < want) rows /= 2;
+            set_layout(rows, 1, fit_threads(256), 1);
+        }
         // explicit override "rows,order,threads,nt[,block]" for experiments
         if (const char *env = getenv("MXS_STENCIL_TILE")) {
             int r = 0, o = 0, t = 0, nt = 1, blk = 0, xs = 0;
             const int k = sscanf(env, "%d,%d,%d,%d,%d,%d", &r, &o, &t, &nt, &blk, &xs);
             if (k >= 3 && r > 0 && (o == 0 || o == 1 || o == 2) && (t == 64 || t == 128 || t == 256) &&
-                (blk == 0 || stencil2d_block_ok(nwx, nwy, blk)) &&
-                (xs == 0 || stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, blk)) &&
+                (blk == 0 || (xs ? stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, blk)
+                                 : stencil2d_block_ok(dtype, nwx, nwy, blk))) &&
                 stencil2d_lds_bytes(dtype, nwx, nwy, t, blk, xs) <= static_cast<size_t>(device_lds_limit()))
                 set_layout(r, o, t, nt != 0, blk, xs);
         }
@@ -215,7 +237,6 @@ struct Stencil2DPlan final : mxs_plan_s {
             return fail(MXS_ERR_ALIAS, "in and out overlap; stencils must write out of place");
         a.in = in;
         a.out = out;
-        a.vec_ok = (a.ld % vec_elems(dtype) == 0) && vec_aligned(in, dtype) && vec_aligned(out, dtype);
         return MXS_OK;
     }
 
@@ -248,7 +269,6 @@ struct Stencil1DPlan final : mxs_plan_s {
             return fail(MXS_ERR_ALIAS, "in and out overlap; stencils must write out of place");
         a.in = in;
         a.out = out;
-        a.vec_ok = vec_aligned(in, dtype) && vec_aligned(out, dtype);
         return MXS_OK;
     }
     mxs_status compute(hipStream_t s) override {
@@ -300,10 +320,12 @@ mxs_status Stencil2DPlan::autotune(hipStream_t s) {
         }
     }
     // block form: all input rows of a chunk requested at once
-    for (int block : {8, 12, 16}) {
-        if (!stencil2d_block_ok(nwx, nwy, block) || block - nwy + 1 > 2 * a.ny) continue;
+    for (int block : {4, 8, 12, 16}) {
+        if (block - nwy + 1 > 2 * a.ny) continue;
         for (int xs : {0, 1}) {
-            if (xs && !stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, block)) continue;
+            if (!(xs ? stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, block)
+                     : stencil2d_block_ok(dtype, nwx, nwy, block)))
+                continue;
             for (int nthreads : {256, 128}) {
                 if (stencil2d_lds_bytes(dtype, nwx, nwy, nthreads, block, xs) > lds_limit) continue;
                 for (int order : {1, 0, 2})

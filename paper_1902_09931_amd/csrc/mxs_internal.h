@@ -40,14 +40,17 @@ __device__ __forceinline__ float bf16_to_float(uint16_t b) {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
-// float -> bfloat16, round to nearest, ties to even; NaN stays NaN.
-__device__ __forceinline__ uint16_t float_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu))
-        return static_cast<uint16_t>((u >> 16) | 0x0040u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return static_cast<uint16_t>(u >> 16);
+// float -> bfloat16, round to nearest, ties to even; NaN stays NaN.  One
+// conversion instruction for two values (it was 8 integer instructions per
+// value, which bounded the bfloat16 stencils: the 5-point x stencil of an
+// 8192^2 grid 80 -> 57 us); equal to the integer form for every float.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t floats_to_bf16x2(float lo, float hi) {
+    const f32x2_t v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
+__device__ __forceinline__ uint16_t float_to_bf16(float f) { return static_cast<uint16_t>(floats_to_bf16x2(f, f)); }
 
 template <typename T> __device__ __forceinline__ typename St<T>::acc to_acc(T v);
 template <> __device__ __forceinline__ double to_acc<double>(double v) { return v; }
@@ -59,20 +62,6 @@ template <> __device__ __forceinline__ double from_acc<double>(double v) { retur
 template <> __device__ __forceinline__ float from_acc<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16 from_acc<bf16>(float v) { return bf16{float_to_bf16(v)}; }
 
-// Vector load/store of St<T>::V consecutive elements (16 bytes: 2 doubles, 4
-// floats or 8 bfloat16s).  The address must be aligned to 16 bytes.
-template <typename T>
-__device__ __forceinline__ void load_vec(const T *p, typename St<T>::acc *x);
-template <>
-__device__ __forceinline__ void load_vec<double>(const double *p, double *x) {
-    double2 v = *reinterpret_cast<const double2 *>(p);
-    x[0] = v.x; x[1] = v.y;
-}
-template <>
-__device__ __forceinline__ void load_vec<float>(const float *p, float *x) {
-    float4 v = *reinterpret_cast<const float4 *>(p);
-    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-}
 // 8 bfloat16s from / to 4 packed words
 __device__ __forceinline__ void unpack_bf16x8(const uint32_t (&w)[4], float *x) {
 #pragma unroll
@@ -83,58 +72,19 @@ __device__ __forceinline__ void unpack_bf16x8(const uint32_t (&w)[4], float *x) 
 }
 __device__ __forceinline__ void pack_bf16x8(const float *x, uint32_t (&w)[4]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        w[k] = static_cast<uint32_t>(float_to_bf16(x[2 * k])) | (static_cast<uint32_t>(float_to_bf16(x[2 * k + 1])) << 16);
-}
-template <>
-__device__ __forceinline__ void load_vec<bf16>(const bf16 *p, float *x) {
-    const uint4 v = *reinterpret_cast<const uint4 *>(p);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    unpack_bf16x8(w, x);
+    for (int k = 0; k < 4; ++k) w[k] = floats_to_bf16x2(x[2 * k], x[2 * k + 1]);
 }
 
-template <typename T>
-__device__ __forceinline__ void store_vec(T *p, const typename St<T>::acc *x);
-template <>
-__device__ __forceinline__ void store_vec<double>(double *p, const double *x) {
-    *reinterpret_cast<double2 *>(p) = make_double2(x[0], x[1]);
-}
-template <>
-__device__ __forceinline__ void store_vec<float>(float *p, const float *x) {
-    *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
-}
-template <>
-__device__ __forceinline__ void store_vec<bf16>(bf16 *p, const float *x) {
-    uint32_t w[4];
-    pack_bf16x8(x, w);
-    *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// Streaming (non-temporal) vector stores: the line is written without being
-// kept in the caches, leaving L2 to the inputs that are read again.
+// 16-byte vectors: v2d_t, v4f_t and v4u_t aligned to 16 bytes (LDS), the _e
+// types to their element (global memory, where a 16-byte access needs the
+// alignment of its element only).
 typedef double v2d_t __attribute__((ext_vector_type(2)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef unsigned int v2u_t __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u_t __attribute__((ext_vector_type(4)));
-template <typename T>
-__device__ __forceinline__ void store_vec_nt(T *p, const typename St<T>::acc *x);
-template <>
-__device__ __forceinline__ void store_vec_nt<double>(double *p, const double *x) {
-    v2d_t v = {x[0], x[1]};
-    __builtin_nontemporal_store(v, reinterpret_cast<v2d_t *>(p));
-}
-template <>
-__device__ __forceinline__ void store_vec_nt<float>(float *p, const float *x) {
-    v4f_t v = {x[0], x[1], x[2], x[3]};
-    __builtin_nontemporal_store(v, reinterpret_cast<v4f_t *>(p));
-}
-template <>
-__device__ __forceinline__ void store_vec_nt<bf16>(bf16 *p, const float *x) {
-    uint32_t w[4];
-    pack_bf16x8(x, w);
-    v4u_t v = {w[0], w[1], w[2], w[3]};
-    __builtin_nontemporal_store(v, reinterpret_cast<v4u_t *>(p));
-}
+typedef double v2d_e __attribute__((ext_vector_type(2), aligned(8)));
+typedef float v4f_e __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int v4u_e __attribute__((ext_vector_type(4), aligned(2)));
 
 // Element access through global-memory pointers (bf16 by its bits).
 template <typename T, typename I> __device__ __forceinline__ T gld(gptr<const T> p, I i) {
@@ -146,62 +96,58 @@ template <typename T, typename I> __device__ __forceinline__ void gst(gptr<T> p,
     else p[i] = v;
 }
 
-// The same vector accesses through global-memory pointers.
+// Load of St<T>::V consecutive elements (16 bytes: 2 doubles, 4 floats or 8
+// bfloat16s) from global memory at any element, in the accumulation type.
 template <typename T>
-__device__ __forceinline__ void load_vec(gptr<const T> p, typename St<T>::acc *x);
-template <>
-__device__ __forceinline__ void load_vec<double>(gptr<const double> p, double *x) {
-    const v2d_t v = *reinterpret_cast<gptr<const v2d_t>>(p);
-    x[0] = v.x; x[1] = v.y;
+__device__ __forceinline__ void load_vec(gptr<const T> p, typename St<T>::acc *x) {
+    if constexpr (std::is_same<T, double>::value) {
+        const v2d_e v = *reinterpret_cast<gptr<const v2d_e>>(p);
+        x[0] = v.x; x[1] = v.y;
+    } else if constexpr (std::is_same<T, float>::value) {
+        const v4f_e v = *reinterpret_cast<gptr<const v4f_e>>(p);
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else {
+        const v4u_e v = *reinterpret_cast<gptr<const v4u_e>>(p);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        unpack_bf16x8(w, x);
+    }
 }
-template <>
-__device__ __forceinline__ void load_vec<float>(gptr<const float> p, float *x) {
-    const v4f_t v = *reinterpret_cast<gptr<const v4f_t>>(p);
-    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+template <typename T> __device__ __forceinline__ void load_vec(const T *p, typename St<T>::acc *x) {
+    load_vec<T>(as_global(p), x);
 }
-template <>
-__device__ __forceinline__ void load_vec<bf16>(gptr<const bf16> p, float *x) {
-    const v4u_t v = *reinterpret_cast<gptr<const v4u_t>>(p);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    unpack_bf16x8(w, x);
+
+// The matching stores; NT: streaming (non-temporal), written without being
+// kept in the caches, leaving L2 to the inputs that are read again.
+template <typename T, bool NT>
+__device__ __forceinline__ void put_vec(gptr<T> p, const typename St<T>::acc *x) {
+    if constexpr (std::is_same<T, double>::value) {
+        const v2d_e v = {x[0], x[1]};
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<v2d_e>>(p));
+        else *reinterpret_cast<gptr<v2d_e>>(p) = v;
+    } else if constexpr (std::is_same<T, float>::value) {
+        const v4f_e v = {x[0], x[1], x[2], x[3]};
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<v4f_e>>(p));
+        else *reinterpret_cast<gptr<v4f_e>>(p) = v;
+    } else {
+        uint32_t w[4];
+        pack_bf16x8(x, w);
+        const v4u_e v = {w[0], w[1], w[2], w[3]};
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<v4u_e>>(p));
+        else *reinterpret_cast<gptr<v4u_e>>(p) = v;
+    }
 }
-template <typename T>
-__device__ __forceinline__ void store_vec(gptr<T> p, const typename St<T>::acc *x);
-template <>
-__device__ __forceinline__ void store_vec<double>(gptr<double> p, const double *x) {
-    const v2d_t v = {x[0], x[1]};
-    *reinterpret_cast<gptr<v2d_t>>(p) = v;
+template <typename T> __device__ __forceinline__ void store_vec(gptr<T> p, const typename St<T>::acc *x) { put_vec<T, false>(p, x); }
+template <typename T> __device__ __forceinline__ void store_vec(T *p, const typename St<T>::acc *x) { put_vec<T, false>(as_global(p), x); }
+// (The empty statements around a streaming store keep the compiler from
+// merging it with a plain store on the other side of a branch, which would
+// make it a plain one: 4096^2 FP64 x stencil 53 -> 59 us.)
+template <typename T> __device__ __forceinline__ void store_vec_nt(gptr<T> p, const typename St<T>::acc *x) {
+    asm volatile("");
+    put_vec<T, true>(p, x);
+    asm volatile("");
 }
-template <>
-__device__ __forceinline__ void store_vec<float>(gptr<float> p, const float *x) {
-    const v4f_t v = {x[0], x[1], x[2], x[3]};
-    *reinterpret_cast<gptr<v4f_t>>(p) = v;
-}
-template <>
-__device__ __forceinline__ void store_vec<bf16>(gptr<bf16> p, const float *x) {
-    uint32_t w[4];
-    pack_bf16x8(x, w);
-    const v4u_t v = {w[0], w[1], w[2], w[3]};
-    *reinterpret_cast<gptr<v4u_t>>(p) = v;
-}
-template <typename T>
-__device__ __forceinline__ void store_vec_nt(gptr<T> p, const typename St<T>::acc *x);
-template <>
-__device__ __forceinline__ void store_vec_nt<double>(gptr<double> p, const double *x) {
-    v2d_t v = {x[0], x[1]};
-    __builtin_nontemporal_store(v, reinterpret_cast<gptr<v2d_t>>(p));
-}
-template <>
-__device__ __forceinline__ void store_vec_nt<float>(gptr<float> p, const float *x) {
-    v4f_t v = {x[0], x[1], x[2], x[3]};
-    __builtin_nontemporal_store(v, reinterpret_cast<gptr<v4f_t>>(p));
-}
-template <>
-__device__ __forceinline__ void store_vec_nt<bf16>(gptr<bf16> p, const float *x) {
-    uint32_t w[4];
-    pack_bf16x8(x, w);
-    v4u_t v = {w[0], w[1], w[2], w[3]};
-    __builtin_nontemporal_store(v, reinterpret_cast<gptr<v4u_t>>(p));
+template <typename T> __device__ __forceinline__ void store_vec_nt(T *p, const typename St<T>::acc *x) {
+    store_vec_nt<T>(as_global(p), x);
 }
 
 __device__ __forceinline__ long long wrap_ll(long long k, long long n) {
@@ -257,12 +203,11 @@ struct Stencil2DArgs {
     int rows;               // output rows per workgroup
     int nchunks;            // row chunks per strip
     int nstrips;            // column strips
-    int vec_ok;             // 16-byte aligned rows
     int order;              // tile order: 0 = each XCD a contiguous run of row chunks
                             // of one strip; 1 = row-major sweep (strips fastest);
                             // 2 = each XCD a contiguous band of chunks, row-major
     int nt_store;           // 1: non-temporal output stores
-    int block_rows;         // 0: streaming form; 8 or 16: block form reading
+    int block_rows;         // 0: streaming form; 4 .. 16: block form reading
                             // that many input rows per workgroup at once
                             // (rows = block_rows - NWY + 1 output rows)
     int xshuffle;           // block form, centred windows: x neighbours by
@@ -289,7 +234,6 @@ struct Stencil1DArgs {
     double coe_d[kMaxCoe];
     float coe_f[kMaxCoe];
     int max_sig_per_tile;       // LDS slots reserved for offsets
-    int vec_ok;
 };
 
 // Window buckets: padded widths the kernels are compiled for.
@@ -303,10 +247,16 @@ size_t stencil2d_lds_bytes(int dtype, int nwx, int nwy, int threads, int block_r
 // Read `bytes` (a multiple of 16) of a device buffer once, so that the
 // memory-side cache holds none of the data timed next.
 hipError_t launch_cache_flush(void *buf, size_t bytes, hipStream_t s);
-// Whether the block form is compiled for this padded window and row count.
-bool stencil2d_block_ok(int nwx, int nwy, int block_rows);
+// Block form, one per storage type.
+hipError_t launch_stencil2d_block_f64(int nwx, int nwy, const Stencil2DArgs &a, int threads, hipStream_t s);
+hipError_t launch_stencil2d_block_f32(int nwx, int nwy, const Stencil2DArgs &a, int threads, hipStream_t s);
+hipError_t launch_stencil2d_block_bf16(int nwx, int nwy, const Stencil2DArgs &a, int threads, hipStream_t s);
+// Whether the block form with x neighbours from LDS rows is compiled for this
+// padded window and row count.
+bool stencil2d_block_ok(int dtype, int nwx, int nwy, int block_rows);
 // Whether the block form can take x neighbours from neighbouring lanes
-// (centred windows of padded width nwx, at most one vector on each side).
+// (centred windows of padded width nwx, at most one vector on each side);
+// windows along x alone have this form of it only.
 bool stencil2d_xshuffle_ok(int dtype, int nwx, int nwy, int left, int right, int block_rows);
 size_t stencil1d_lds_bytes(int dtype, int nwx, int threads, int max_sig);
 

@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const long long eb = e0 + static_cast<long long>(u * nt + t) * V;
-        if (a.vec_ok && eb + V <= a.total) {
+        if (eb + V <= a.total) {
             load_vec<T>(in + eb, xv[u]);
         } else {
 #pragma unroll
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
         // the common case: the whole vector lies in one signal with every
         // window inside it (no wrap, every output written): straight-line
         // FMAs over the staged values
-        if (a.vec_ok && eb >= sb + a.L && eb + V - 1 + a.R <= se - 1) {
+        if (eb >= sb + a.L && eb + V - 1 + a.R <= se - 1) {
             const A *lp = lds + PAD + (eb - e0) - a.L;
             A x[V + NWX - 1];
 #pragma unroll
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
             }
             res[v] = acc;
         }
-        bool all = a.vec_ok && eb + V <= a.total;
+        bool all = eb + V <= a.total;
 #pragma unroll
         for (int v = 0; v < V; ++v) all = all && wr[v];
         if (all) {

@@ -1,0 +1,10 @@
+// 2D stencils in block form, bfloat16 storage.
+#include "stencil2d_block_dev.h"
+
+namespace mxs {
+
+hipError_t launch_stencil2d_block_bf16(int nwx, int nwy, const Stencil2DArgs &a, int threads, hipStream_t s) {
+    return dispatch_block<bf16>(nwx, nwy, a, threads, s);
+}
+
+}  // namespace mxs

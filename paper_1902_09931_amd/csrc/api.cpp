@@ -513,7 +513,8 @@ mxs_status mxs_create_1d_batch(int nbatch, const long long *offsets, int bc, int
         delete p;
         return st;
     }
-    const int W = p->threads * vec_elems(dtype) * kS1dVecs;
+    p->a.vecs = total < static_cast<long long>(p->threads) * vec_elems(dtype) * kS1dVecs * device_cu_count() ? 1 : kS1dVecs;
+    const int W = p->threads * vec_elems(dtype) * p->a.vecs;
     const long long ntiles = (total + W - 1) / W;
     if (ntiles >= (1LL << 31)) {
         delete p;
@@ -530,7 +531,7 @@ mxs_status mxs_create_1d_batch(int nbatch, const long long *offsets, int bc, int
         if (t > 0) maxsig = std::max(maxsig, tf[t] - tf[t - 1] + 2);
     }
     p->a.max_sig_per_tile = std::max(maxsig, 2);
-    if (stencil1d_lds_bytes(dtype, nwx, p->threads, p->a.max_sig_per_tile) >
+    if (stencil1d_lds_bytes(dtype, nwx, p->threads, p->a.max_sig_per_tile, p->a.vecs) >
         static_cast<size_t>(device_lds_limit())) {
         delete p;
         return fail(MXS_ERR_UNSUPPORTED, "signals too short for the LDS budget");

@@ -215,8 +215,9 @@ struct Stencil2DArgs {
 };
 
 // Vectors per thread in one tile of the batched 1D stencil (a tile is
-// threads * V * kS1dVecs elements, so one workgroup has that many bytes in
-// flight at once).
+// threads * V * vecs elements, so one workgroup has that many bytes in
+// flight at once): kS1dVecs, or 1 for batches that would otherwise leave CUs
+// without a workgroup, where a thread's vectors only follow one another.
 constexpr int kS1dVecs = 4;
 
 struct Stencil1DArgs {
@@ -227,6 +228,7 @@ struct Stencil1DArgs {
     long long total;
     int nbatch;
     int ntiles;
+    int vecs;                   // vectors per thread: 1 or kS1dVecs
     int L, R;
     int periodic;
     int ncoe;
@@ -258,6 +260,6 @@ bool stencil2d_block_ok(int dtype, int nwx, int nwy, int block_rows);
 // (centred windows of padded width nwx, at most one vector on each side);
 // windows along x alone have this form of it only.
 bool stencil2d_xshuffle_ok(int dtype, int nwx, int nwy, int left, int right, int block_rows);
-size_t stencil1d_lds_bytes(int dtype, int nwx, int threads, int max_sig);
+size_t stencil1d_lds_bytes(int dtype, int nwx, int threads, int max_sig, int vecs);
 
 }  // namespace mxs

@@ -35,11 +35,10 @@ template <int NWX, int V> constexpr int halo_pad() {
     return NWX > 1 ? ((NWX - 1 + V - 1) / V) * V : 0;
 }
 
-template <typename T, int NWX>
+template <typename T, int NWX, int U>
 __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
     using A = typename St<T>::acc;
     constexpr int V = St<T>::V;
-    constexpr int U = kS1dVecs;
     constexpr int PAD = halo_pad<NWX, V>();
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -130,6 +129,55 @@ __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
             put_vec<T>(out + eb, res);
             continue;
         }
+        // a vector that meets one signal end at most: its elements are in the
+        // signal [sb, se) or in the next one, so two windows cover them, each
+        // with the taps past its own signal's ends read from where they wrap
+        // to; every such read is requested before any is used
+        if (eb + V <= a.total && (se >= eb + V || soff[lo + 2] >= eb + V)) {
+            const bool cross = se < eb + V;
+            const long long sb2 = cross ? se : sb, se2 = cross ? soff[lo + 2] : se;
+            const A *lp = lds + PAD + (eb - e0) - a.L;
+            A x[V + NWX - 1], y[V + NWX - 1];
+#pragma unroll
+            for (int k = 0; k < V + NWX - 1; ++k) {
+                x[k] = y[k] = lp[k];
+                const long long idx = eb - a.L + k;
+                if (periodic && k < V + taps - 1) {
+                    const long long ix = idx < sb ? idx + (se - sb) : idx >= se ? idx - (se - sb) : idx;
+                    const long long iy = idx < sb2 ? idx + (se2 - sb2) : idx >= se2 ? idx - (se2 - sb2) : idx;
+                    if (ix != idx) x[k] = to_acc<T>(in[ix]);
+                    if (iy != idx) y[k] = to_acc<T>(in[iy]);
+                }
+            }
+            if (a.ncoe && periodic) {
+#pragma unroll
+                for (int k = 0; k < V + NWX - 1; ++k) {
+                    const long long idx = eb - a.L + k;
+                    if (k < V + taps - 1 && (idx < sb || idx >= se)) x[k] = point_fun<A>(x[k], coe, a.ncoe);
+                    if (k < V + taps - 1 && (idx < sb2 || idx >= se2)) y[k] = point_fun<A>(y[k], coe, a.ncoe);
+                }
+            }
+            bool all = true;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const bool second = eb + v >= se;
+                A acc = A(0);
+#pragma unroll
+                for (int p = 0; p < NWX; ++p) acc = fma(w[p], second ? y[v + p] : x[v + p], acc);
+                res[v] = acc;
+                const long long i = eb + v - (second ? sb2 : sb), n = second ? se2 - sb2 : se - sb;
+                wr[v] = periodic || (i >= a.L && i <= n - 1 - a.R);
+                all = all && wr[v];
+            }
+            if (all) {
+                put_vec<T>(out + eb, res);
+            } else {
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (wr[v]) out[eb + v] = from_acc<T>(res[v]);
+            }
+            continue;
+        }
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const long long e = eb + v;
@@ -185,8 +233,13 @@ template <typename T, int NWX>
 hipError_t launch_one(const Stencil1DArgs &a, int threads, int grid, hipStream_t s) {
     const size_t lds = stencil1d_lds_bytes(std::is_same<T, double>::value ? F64
                                            : std::is_same<T, float>::value ? F32 : BF16,
-                                           NWX, threads, a.max_sig_per_tile);
-    hipLaunchKernelGGL((stencil1d_kernel<T, NWX>), dim3(grid), dim3(threads), lds, s, a);
+                                           NWX, threads, a.max_sig_per_tile, a.vecs);
+    if (a.vecs == kS1dVecs)
+        hipLaunchKernelGGL((stencil1d_kernel<T, NWX, kS1dVecs>), dim3(grid), dim3(threads), lds, s, a);
+    else if (a.vecs == 1)
+        hipLaunchKernelGGL((stencil1d_kernel<T, NWX, 1>), dim3(grid), dim3(threads), lds, s, a);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -204,11 +257,11 @@ hipError_t dispatch(int nwx, const Stencil1DArgs &a, int threads, int grid, hipS
 
 }  // namespace
 
-size_t stencil1d_lds_bytes(int dtype, int nwx, int threads, int max_sig) {
+size_t stencil1d_lds_bytes(int dtype, int nwx, int threads, int max_sig, int vecs) {
     const int V = dtype == F64 ? St<double>::V : dtype == F32 ? St<float>::V : St<bf16>::V;
     const int acc = dtype == F64 ? 8 : 4;
     const int pad = nwx > 1 ? ((nwx - 1 + V - 1) / V) * V : 0;
-    const size_t vals = (static_cast<size_t>(2 * pad + threads * V * kS1dVecs) * acc + 15) & ~static_cast<size_t>(15);
+    const size_t vals = (static_cast<size_t>(2 * pad + threads * V * vecs) * acc + 15) & ~static_cast<size_t>(15);
     return vals + static_cast<size_t>(max_sig) * sizeof(long long);
 }
 

@@ -24,6 +24,12 @@ namespace mxs {
 
 namespace {
 
+// Address of a byte offset from a uniform base (one 32-bit register per lane).
+template <typename T> __device__ __forceinline__ gptr<T> at_byte(gptr<T> base, unsigned o) {
+    using C = std::conditional_t<std::is_const<T>::value, const char, char>;
+    return (gptr<T>)((gptr<C>)base + o);
+}
+
 // 4 consecutive values from global memory (16-byte aligned; 8 for bfloat16)
 __device__ __forceinline__ void load4(gptr<const double> p, double *x) {
     load_vec<double>(p, x);
@@ -91,8 +97,14 @@ template <typename TW, int LPR> struct QuadLds {
     static constexpr size_t bytes = xch + sizeof(double2) * kQuadRows<LPR> * kGroupXch<LPR>;
 };
 
+// Wavefronts per SIMD the registers are bounded to: double holds 4 (128
+// registers, no spills), float 5 with 3 rows requested ahead (94 registers;
+// 4096^2 131.5 -> 128.6 us a step, 64-grid ensemble 248 -> 245; at 6, or 5 in
+// double, the kernel spills and loses 15 to 25%).
+template <typename T> constexpr int kQuadWaves = sizeof(T) == 8 ? 4 : 5;
+
 template <typename T, typename TW, int LPR>
-__global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const RhsInst *__restrict__ rhs,
+__global__ void __launch_bounds__(kQuadRows<LPR> *LPR, kQuadWaves<T>) ch_quads_kernel(const RhsInst *__restrict__ rhs,
                                                                        const RowsInst *__restrict__ rows,
                                                                        const RowGroup *__restrict__ work, int count) {
     using A = typename St<T>::acc;
@@ -101,7 +113,7 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
     constexpr int QPT = 4 * LPR / NT;      // quads per thread, NT apart
     constexpr bool ONE = NT <= 64;         // one wavefront per workgroup
     // Input rows requested ahead of the one being used.
-    constexpr int AHEAD = sizeof(A) == 8 ? 2 : 5;
+    constexpr int AHEAD = sizeof(A) == 8 ? 2 : 3;
     // In double the terms of a value are added as their rows arrive.  In
     // float every value is summed in the order of ch_rhs_rows_kernel (the 13
     // taps, then the 5, then the difference), so that both kernels round
@@ -144,11 +156,13 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
 
         if (q0 < nq) {
             const int lv = min(63, nq - 1 - q0);   // the wavefront's last lane with a quad
-            const long long col = 4 * (valid ? qd : nq - 1);
+            // lanes past the row's end load its first quad: the first of them
+            // is then the right neighbour of the row's last quad
+            const unsigned ob = (valid ? 4u * static_cast<unsigned>(qd) : 0u) * sizeof(T);
 
             // halo: lanes 0 .. 4 GIN - 1 load column slot lane % 4 (two
-            // before the wavefront's first column, two after its last) of
-            // input row lane / 4
+            // before the wavefront's first column, two after its 64 quads or
+            // the row's last) of input row lane / 4
             const int hu = min(lane >> 2, GIN - 1), hh = lane & 3;
             const int hc = wrap_near(hh < 2 ? 4 * q0 - 2 + hh : 4 * (q0 + lv) + 2 + hh, nx);
             const long long ho = static_cast<long long>(wrap_near(j0 - 2 + hu, ny)) * nx + hc;
@@ -157,8 +171,8 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
             A c[GIN][4], q[GIN][4];
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
-                load4(cur + (roff[u] + col), c[u]);
-                load4(prev + (roff[u] + col), q[u]);
+                load4(at_byte(cur + roff[u], ob), c[u]);
+                load4(at_byte(prev + roff[u], ob), q[u]);
             }
 
             // the halo values to the wavefront's end lanes, through LDS space
@@ -175,8 +189,8 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
 #pragma unroll
             for (int u = 0; u < GIN; ++u) {
                 if (u + AHEAD < GIN) {
-                    load4(cur + (roff[u + AHEAD] + col), c[u + AHEAD]);
-                    load4(prev + (roff[u + AHEAD] + col), q[u + AHEAD]);
+                    load4(at_byte(cur + roff[u + AHEAD], ob), c[u + AHEAD]);
+                    load4(at_byte(prev + roff[u + AHEAD], ob), q[u + AHEAD]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 A x[8], f[6];   // Cbar at the quad and two columns on each side; C^3 - C with one
@@ -187,15 +201,13 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) f[1 + i] = A(0);
                 if (u >= 1 && u < GIN - 1) {
-                    A hb[4];   // the row's halo: two columns before lane 0, two after lane lv
+                    A hb[4];   // the row's halo: two columns before lane 0, two after lane 63
                     lds4(hal + 4 * u, hb);
                     x[1] = lane_shift<kPrevLane>(x[5], hb[1]);
-                    const A r1 = lane_shift<kNextLane>(x[2], hb[2]);
-                    x[6] = lane == lv ? hb[2] : r1;
+                    x[6] = lane_shift<kNextLane>(x[2], hb[2]);
                     if (u >= 2 && u < GIN - 2) {
                         x[0] = lane_shift<kPrevLane>(x[4], hb[0]);
-                        const A r2 = lane_shift<kNextLane>(x[3], hb[3]);
-                        x[7] = lane == lv ? hb[3] : r2;
+                        x[7] = lane_shift<kNextLane>(x[3], hb[3]);
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) f[1 + i] = c[u][i] * c[u][i] * c[u][i] - c[u][i];
@@ -203,8 +215,7 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
                         A hf[4];
                         lds4(hal + 32 + 4 * u, hf);
                         f[0] = lane_shift<kPrevLane>(f[4], hf[1]);
-                        const A rf = lane_shift<kNextLane>(f[1], hf[2]);
-                        f[5] = lane == lv ? hf[2] : rf;
+                        f[5] = lane_shift<kNextLane>(f[1], hf[2]);
                     }
                 }
                 if constexpr (ORDERED) {
@@ -250,11 +261,17 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
 
         // R to LDS, zero past the row's end
         wave_sync();
+        if (!valid) {
+#pragma unroll
+            for (int r = 0; r < WR; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[r][i] = A(0);
+        }
 #pragma unroll
         for (int r = 0; r < WR; ++r) {
             TW x[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = valid ? static_cast<TW>(acc[r][i]) : TW(0);
+            for (int i = 0; i < 4; ++i) x[i] = static_cast<TW>(acc[r][i]);
             lds4_set(mine + r * Lds::ROW, x);
         }
     }
@@ -293,7 +310,8 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, 4) ch_quads_kernel(const 
         for (int k = 0; k < WR; ++k) {
             TW x[4];
             lds4(mine + k * Lds::ROW, x);
-            if (qd < nq && j0 + k < ny) store4(out + ((j0 + k) * RI.ld + 4 * qd), x);
+            if (qd < nq && j0 + k < ny)
+                store4(at_byte(out + (j0 + k) * RI.ld, 4u * static_cast<unsigned>(qd) * static_cast<unsigned>(sizeof(TW))), x);
         }
     }
 }

@@ -146,10 +146,19 @@ def _ptr(buf):
     return int(buf)
 
 
+def _current_stream():
+    """Handle of torch's current stream on the current device.  Asked for by
+    handle: torch.cuda.current_stream() builds a Stream object, 2.7 us of a
+    5.9 us call on a small grid."""
+    import torch
+    device = torch.cuda.current_device()      # initialises torch's device state
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(device)
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream
     return int(stream)

@@ -136,3 +136,13 @@ def test_fused_replays_with_strips_equal_eager_steps():
         runs.append(states)
     assert all(torch.equal(x, y) for x, y in zip(*runs))
     assert rel_err(runs[0][-1].cpu().numpy(), runs[1][-1].cpu().numpy()) == 0.0
+
+
+def test_default_stream_is_torchs_current_stream():
+    """Calls without a stream run on torch's current one, inside and outside
+    a stream context."""
+    assert b._stream(None) == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert b._stream(None) == s.cuda_stream
+    assert b._stream(None) == torch.cuda.current_stream().cuda_stream

@@ -77,9 +77,15 @@ constexpr int kWX = MXS_L + MXS_R + 1, kWY = MXS_T + MXS_B + 1, kNWIN = kWX * kW
 constexpr int kLoc = MXS_T * kWX + MXS_L;
 constexpr int kTW = MXS_NT + MXS_L + MXS_R, kTH = MXS_ROWS + MXS_T + MXS_B;
 
+// k inside [0, n): wrapped or clamped.  Tiles reach at most a window before the
+// grid and a tile past it, so the division is for grids smaller than a tile
+// only (two divisions per staged value were most of the kernel's time).
 __device__ __forceinline__ long long mxs_fix(long long k, long long n) {
-    if (MXS_PERIODIC) { k %%= n; return k < 0 ? k + n : k; }
-    return k < 0 ? 0 : (k >= n ? n - 1 : k);
+    if (!MXS_PERIODIC) return k < 0 ? 0 : (k >= n ? n - 1 : k);
+    if (k < 0) k += n;
+    else if (k >= n) k -= n;
+    if (k < 0 || k >= n) { k %%= n; if (k < 0) k += n; }
+    return k;
 }
 #define MXS_GLOBAL __attribute__((address_space(1)))
 __device__ __forceinline__ mxs_real mxs_load(const void *p, long long i) {
@@ -104,15 +110,31 @@ __device__ __forceinline__ void mxs_store(void *p, long long i, mxs_real v) {
 extern "C" __global__ void __launch_bounds__(MXS_NT) mxs_user_stencil(const FnArgs a) {
     extern __shared__ mxs_real mxs_tile[];
     const int strip = blockIdx.x %% a.nstrips, chunk = blockIdx.x / a.nstrips;
-    const long long i0 = static_cast<long long>(strip) * MXS_NT;
-    const long long j0 = static_cast<long long>(chunk) * MXS_ROWS;
+    const long long i0 = static_cast<long long>(strip) * MXS_NT, j0 = static_cast<long long>(chunk) * MXS_ROWS;
+    // the tile of every input, kLD values per thread requested before any is stored
+    constexpr int kN = (kTH * kTW + MXS_NT - 1) / MXS_NT, kLD = kN < 12 ? kN : 12;
+#pragma unroll 1
+    for (int g = 0; g < kN; g += kLD) {
+        mxs_real v[MXS_NIN][kLD];
 #pragma unroll
-    for (int k = 0; k < MXS_NIN; ++k)
-        for (int e = threadIdx.x; e < kTH * kTW; e += MXS_NT) {
-            const int r = e / kTW, c = e - r * kTW;
-            const long long J = mxs_fix(j0 - MXS_T + r, a.ny), I = mxs_fix(i0 - MXS_L + c, a.nx);
-            mxs_tile[(k * kTH + r) * kTW + c] = mxs_load(a.in[k], J * a.ld + I);
+        for (int u = 0; u < kLD; ++u) {
+            const int e = (g + u) * MXS_NT + threadIdx.x;
+            if (e < kTH * kTW) {
+                const int r = e / kTW, c = e - r * kTW;
+                const long long o = mxs_fix(j0 - MXS_T + r, a.ny) * a.ld + mxs_fix(i0 - MXS_L + c, a.nx);
+#pragma unroll
+                for (int k = 0; k < MXS_NIN; ++k) v[k][u] = mxs_load(a.in[k], o);
+            }
         }
+#pragma unroll
+        for (int u = 0; u < kLD; ++u) {
+            const int e = (g + u) * MXS_NT + threadIdx.x;
+            if (e < kTH * kTW) {
+#pragma unroll
+                for (int k = 0; k < MXS_NIN; ++k) mxs_tile[k * kTH * kTW + e] = v[k][u];
+            }
+        }
+    }
     __syncthreads();
     const long long i = i0 + threadIdx.x;
     if (i >= a.nx) return;

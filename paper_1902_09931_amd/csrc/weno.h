@@ -16,7 +16,6 @@ struct WenoArgs {
     int nchunks, nstrips;
     int order;                 // tile order, as for the 2D stencils
     int nt_store;              // non-temporal output stores
-    int vec_ok;                // 16-byte aligned rows of every array
 };
 
 size_t weno_lds_bytes(int rows, int threads);

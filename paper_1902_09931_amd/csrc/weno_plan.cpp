@@ -14,7 +14,6 @@ namespace mxs {
 
 namespace {
 
-bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 struct WenoPlan final : mxs_plan_s {
     WenoArgs a{};
@@ -39,7 +38,6 @@ struct WenoPlan final : mxs_plan_s {
             return fail(MXS_ERR_ALIAS, "out overlaps an input");
         a.phi = phi;
         a.out = out;
-        a.vec_ok = a.ld % 2 == 0 && aligned16(phi) && aligned16(out) && aligned16(a.u) && aligned16(a.v);
         return MXS_OK;
     }
 
@@ -64,8 +62,11 @@ struct WenoPlan final : mxs_plan_s {
             double t;
         };
         std::vector<Cand> cands;
-        for (int rows : {4, 8})
-            for (int nthreads : {256, 128})
+        // one row per workgroup, or one wavefront, only where larger tiles leave CUs without work
+        const bool few = static_cast<long long>(a.nx) * a.ny < 2048LL * 4 * device_cu_count();
+        for (int rows : {1, 4, 8})
+            for (int nthreads : {256, 128, 64})
+                if (few || (rows > 1 && nthreads > 64))
                 for (int order : {1, 0})
                     for (int nt : {1, 0})
                         if (weno_lds_bytes(rows, nthreads) <= static_cast<size_t>(device_lds_limit()))
@@ -134,7 +135,15 @@ mxs_status mxs_create_weno_adv(int nx, int ny, long long ld, double dx, double d
         delete p;
         return st;
     }
-    p->set_layout(8, 1, 256, 1);
+    // A strip that fits in a row; 8 output rows per workgroup, fewer where that
+    // leaves CUs without one (a row is one serial chain of arithmetic).
+    {
+        int nthreads = 256;
+        while (nthreads > 64 && 2 * nthreads > nx) nthreads /= 2;
+        auto tiles = [&](int r) { return static_cast<long long>((nx + 2 * nthreads - 1) / (2 * nthreads)) * ((ny + r - 1) / r); };
+        const long long cus = device_cu_count();
+        p->set_layout(tiles(8) >= 4 * cus ? 8 : tiles(4) >= 2 * cus ? 4 : 1, 1, nthreads, 1);
+    }
     // explicit layout "rows,order,threads,nt" for experiments and tests
     if (const char *env = getenv("MXS_WENO_TILE")) {
         int r = 0, o = 0, t = 0, nt = 1;

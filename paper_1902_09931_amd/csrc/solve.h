@@ -161,17 +161,9 @@ hipError_t launch_ragged_lines(int dtype, int bw, const RaggedLines &a, int nw, 
 // belong to instance 0.
 hipError_t launch_rows(int dtype, int bw, const RowsInst *inst, const int *map, int nlines, int nw,
                        int grid, size_t lds, hipStream_t s);
-// A work unit of the register kernel for ragged lines: `count` consecutive
-// lines (positions first .. first + count - 1 of the sorted order) of length
-// class nb, at most kWaveNBMax / nb of them.
-struct WaveUnit {
-    int first;
-    int count;
-    int nb;
-    int pad;
-};
-// Every work unit in one launch (one wavefront per unit).
-hipError_t launch_wave_units(int dtype, int bw, const RaggedLines &a, const WaveUnit *units, int nunits,
+// Register kernel over ragged lines of any class up to nb in one launch:
+// sorted positions first .. first + count - 1, one wavefront each.
+hipError_t launch_wave_units(int dtype, int bw, int nb, const RaggedLines &a, int first, int count,
                              hipStream_t s);
 // Register kernel over the ragged lines of one class nb: sorted positions
 // first .. first + count - 1, one wavefront each.

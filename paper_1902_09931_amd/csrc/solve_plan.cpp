@@ -33,7 +33,7 @@ struct SolvePlan final : mxs_plan_s {
     CyclicFactor f;
     // ragged
     RaggedLines rl{};
-    DevBuf offsets, order, units;
+    DevBuf offsets, order;
     // rows / cols: the instance table of the current (rhs, x) pair in
     // tables[cur], of the swapped pair in tables[1 - cur]; both are uploaded
     // when the pointers are set, so that compute() only launches (it can be
@@ -46,8 +46,8 @@ struct SolvePlan final : mxs_plan_s {
     int cur = 0;
     // register kernel classes (blocks per line, first line, line count), for
     // plan_info; ragged lines longer than kWaveLineMax (the first nlong in
-    // sorted order) go to the LDS kernel, the others to one launch of the
-    // work-unit kernel
+    // sorted order) go to the LDS kernel, the other nunits to the register
+    // kernels
     struct WaveRange {
         int nb, first, count;
     };
@@ -112,7 +112,7 @@ struct SolvePlan final : mxs_plan_s {
                 for (size_t q = 0; q < wave.size() && e == hipSuccess; ++q)
                     e = launch_wave_ragged(dtype, bw, wave[q].nb, rl, wave[q].first, wave[q].count, s);
             } else if (e == hipSuccess && nunits > 0) {
-                e = launch_wave_units(dtype, bw, rl, static_cast<const WaveUnit *>(units.ptr), nunits, s);
+                e = launch_wave_units(dtype, bw, wave.front().nb, rl, nlong, nunits, s);
             }
         } else if (geometry == MXS_LINES_ROWS) {
             const RowsInst *ti = static_cast<const RowsInst *>(tables[cur].ptr);
@@ -150,9 +150,17 @@ struct SolvePlan final : mxs_plan_s {
         grid = wave_grid(std::max(1, geometry == MXS_LINES_RAGGED ? nlong : nlines), lds);
     }
 
-    // Ragged lines of at most 4096 elements go out either in one launch
-    // (work-unit table; the kernel holds the registers of the largest class)
-    // or in one launch per length class (each with its own registers).
+    // Ragged lines of at most 4096 elements go out either in one launch (the
+    // kernel holds the registers of the largest class) or in one launch per
+    // length class (each with its own registers, each waiting for the one
+    // before it to drain).  One launch pays while the drains cost more than
+    // the lost occupancy.  Lines of 64 .. 4096, one launch / by class, us:
+    // tridiagonal FP64 300 lines 10 / 26, 3000 21 / 40, 20000 143 / 167, 65536
+    // 444 / 462; FP32 lines of 64 .. 1500 20000 36 / 46, 65536 143 / 130.
+    // Pentadiagonal FP64, whose kernel for every class fits one wavefront per
+    // SIMD: 300 lines 12 / 31, 9000 88 / 92, 14000 134 / 135, 20000 188 / 173,
+    // 65536 600 / 470.
+    static int units_max(int bw) { return bw == 1 ? 32768 : 14000; }
     bool per_class = false;
     double tuned_units = 0, tuned_classes = 0;
 
@@ -322,22 +330,10 @@ extern "C" mxs_status mxs_create_cyclic_solve(int bw, const double *coef, int ge
                 q = r;
             }
         }
-        // work units: consecutive lines of one class, kWaveNBMax / nb of
-        // them (the last unit of a class may hold fewer), largest class first
-        std::vector<WaveUnit> units;
-        for (const auto &w : p->wave) {
-            const int per = kWaveNBMax / w.nb;
-            for (int q = 0; q < w.count; q += per)
-                units.push_back({w.first + q, std::min(per, w.count - q), w.nb, 0});
-        }
-        p->nunits = static_cast<int>(units.size());
-        // MXS_RAGGED_FORM=classes starts the plan with one launch per class
+        for (const auto &w : p->wave) p->nunits += w.count;
+        p->per_class = p->wave.size() == 1 || p->nunits > SolvePlan::units_max(bw);
+        // MXS_RAGGED_FORM=classes or units starts the plan with that form
         if (const char *env = getenv("MXS_RAGGED_FORM")) p->per_class = env[0] == 'c';
-        if (!units.empty() &&
-            (e = p->units.upload(units.data(), sizeof(WaveUnit) * units.size())) != hipSuccess) {
-            delete p;
-            return hip_fail(e, "line tables upload");
-        }
         p->rl.offsets = static_cast<const long long *>(p->offsets.ptr);
         p->rl.order = static_cast<const int *>(p->order.ptr);
         p->rl.nlines = p->nlong;

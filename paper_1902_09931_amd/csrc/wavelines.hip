@@ -35,90 +35,30 @@ namespace mxs {
 
 namespace {
 
-// One work unit of ragged lines: `count` consecutive lines (at most K =
-// kWaveNBMax / NB) of length class NB, solved one after the other by the
-// calling wavefront, every element of line q + 1 requested while line q is
-// solved.  Requests past the unit's last line repeat that line (its elements
-// come from the cache) so that the request sequence, and with it the waits
-// for each line's elements, is the same in every unit.  Double-precision
-// pentadiagonal lines of class 8 are not prefetched: the second line's
-// registers would not fit beside the first one's solve without spilling.
-template <typename T, int BW, int NB>
-__device__ __forceinline__ void wave_unit(const RaggedLines &a, int first, int count, T *buf) {
-    constexpr int K = kWaveNBMax / NB;
-    constexpr bool PREFETCH = !(NB == 8 && BW == 2 && sizeof(T) == 8);
-    constexpr int E = WaveShape<NB>::E, NBB = WaveShape<NB>::NBB;
-    const gptr<const T> in = as_global(static_cast<const T *>(a.in));
-    const gptr<const int> order = as_global(a.order);
+// Ragged lines of every class in one launch, one wavefront each: positions
+// first .. first + count - 1 of the sorted order, the class read from the
+// line's length.  NBMAX (4 or 16): the largest class that the kernel holds
+// registers for.  A batch that leaves the chip mostly idle takes the time of
+// one launch and of one line's chain of loads and scans, so no wavefront gets
+// a second line: with up to 16 short lines one after the other in a wavefront,
+// 300 tridiagonal FP64 lines of 64 .. 1500 elements took 24.3 us, 3000 of
+// 64 .. 4096 40.5 us; now 4.9 and 21 us.
+template <typename T, int BW, int NBMAX>
+__global__ void __launch_bounds__(64) wave_units_kernel(const RaggedLines a, int first, int count) {
+    __shared__ __align__(16) T stage[Stage<T, WaveShape<NBMAX>::E>::SIZE];
+    const int k = blockIdx.x;
+    if (k >= count) return;
+    const int b = as_global(a.order)[first + k];
     const gptr<const long long> offs = as_global(a.offsets);
-    auto line_of = [&](int q, long long &base, int &len) __attribute__((always_inline)) {
-        const int b = order[first + min(q, count - 1)];
-        base = offs[b];
-        len = static_cast<int>(offs[b + 1] - base);
-    };
-    auto solve = [&](long long base, int len, T (&raw)[NBB][E]) __attribute__((always_inline)) {
-        LineRef L;
-        L.in = static_cast<const T *>(a.in) + base;
-        L.out = static_cast<T *>(a.out) + base;
-        L.n = len;
-        L.p1 = a.p1;
-        L.p2 = a.p2;
-        L.invK = a.invK;
-        L.pow = a.pow;
-        wave_solve<T, BW, NB>(L, raw, buf);
-    };
-    T ra[NBB][E], rb[NBB][E];
-    long long b0, b1;
-    int n0, n1;
-    line_of(0, b0, n0);
-    wave_fetch<T, NB>(in + b0, n0, ra);
-    if constexpr (!PREFETCH) {
-        solve(b0, n0, ra);
-#pragma unroll
-        for (int q = 1; q < K; ++q) {
-            if (q < count) {
-                line_of(q, b0, n0);
-                wave_fetch<T, NB>(in + b0, n0, ra);
-                solve(b0, n0, ra);
-            }
-        }
-        return;
+    const long long n = offs[b + 1] - offs[b];
+    const RaggedSrc<T> src{a};
+    if constexpr (NBMAX == 16) {
+        if (n > 8 * kWaveBlock) return wave_line<T, BW, 16>(src, first + k, stage);
+        if (n > 4 * kWaveBlock) return wave_line<T, BW, 8>(src, first + k, stage);
     }
-#pragma unroll
-    for (int q = 0; q < K; q += 2) {
-        if (q + 1 < K) {
-            line_of(q + 1, b1, n1);
-            wave_fetch<T, NB>(in + b1, n1, rb);
-        }
-        if (q < count) solve(b0, n0, ra);
-        if (q + 1 < K) {
-            if (q + 2 < K) {
-                line_of(q + 2, b0, n0);
-                wave_fetch<T, NB>(in + b0, n0, ra);
-            }
-            if (q + 1 < count) solve(b1, n1, rb);
-        }
-    }
-}
-
-// Every ragged line of at most kWaveLineMax elements in one launch: one
-// wavefront per workgroup and one work unit per wavefront, the unit's length
-// class read from the unit table (a workgroup's registers are released when
-// its own unit is done, whatever the lengths of the lines beside it).
-template <typename T, int BW>
-__global__ void __launch_bounds__(64) wave_units_kernel(const RaggedLines a,
-                                                        const WaveUnit *__restrict__ units, int nunits) {
-    __shared__ __align__(16) T stage[Stage<T, WaveShape<kWaveNBMax>::E>::SIZE];
-    const int u = blockIdx.x;
-    if (u >= nunits) return;
-    const WaveUnit w = units[u];
-    switch (w.nb) {
-    case 1: wave_unit<T, BW, 1>(a, w.first, w.count, stage); break;
-    case 2: wave_unit<T, BW, 2>(a, w.first, w.count, stage); break;
-    case 4: wave_unit<T, BW, 4>(a, w.first, w.count, stage); break;
-    case 8: wave_unit<T, BW, 8>(a, w.first, w.count, stage); break;
-    default: wave_unit<T, BW, 16>(a, w.first, w.count, stage); break;
-    }
+    if (n > 2 * kWaveBlock) wave_line<T, BW, 4>(src, first + k, stage);
+    else if (n > kWaveBlock) wave_line<T, BW, 2>(src, first + k, stage);
+    else wave_line<T, BW, 1>(src, first + k, stage);
 }
 
 // One ragged line of class NB per wavefront (positions first .. first +
@@ -143,12 +83,16 @@ __global__ void __launch_bounds__(64) wave_rows_kernel(const RowsInst *__restric
 }
 
 template <typename T>
-hipError_t units_bw(int bw, const RaggedLines &a, const WaveUnit *units, int nunits, hipStream_t s) {
-    const dim3 grid(nunits), block(64);
-    if (bw == 2)
-        hipLaunchKernelGGL((wave_units_kernel<T, 2>), grid, block, 0, s, a, units, nunits);
+hipError_t units_bw(int bw, int nb, const RaggedLines &a, int first, int count, hipStream_t s) {
+    const dim3 grid(count), block(64);
+    if (bw == 2 && nb <= 4)
+        hipLaunchKernelGGL((wave_units_kernel<T, 2, 4>), grid, block, 0, s, a, first, count);
+    else if (bw == 2)
+        hipLaunchKernelGGL((wave_units_kernel<T, 2, 16>), grid, block, 0, s, a, first, count);
+    else if (nb <= 4)
+        hipLaunchKernelGGL((wave_units_kernel<T, 1, 4>), grid, block, 0, s, a, first, count);
     else
-        hipLaunchKernelGGL((wave_units_kernel<T, 1>), grid, block, 0, s, a, units, nunits);
+        hipLaunchKernelGGL((wave_units_kernel<T, 1, 16>), grid, block, 0, s, a, first, count);
     return hipGetLastError();
 }
 
@@ -189,14 +133,14 @@ hipError_t rows_bw(int bw, int nb, const RowsInst *inst, const int *map, int fir
 
 }  // namespace
 
-hipError_t launch_wave_units(int dtype, int bw, const RaggedLines &a, const WaveUnit *units, int nunits,
+hipError_t launch_wave_units(int dtype, int bw, int nb, const RaggedLines &a, int first, int count,
                              hipStream_t s) {
-    if (nunits <= 0) return hipSuccess;
+    if (count <= 0) return hipSuccess;
     if (bw != 1 && bw != 2) return hipErrorInvalidValue;
     switch (dtype) {
-    case F64: return units_bw<double>(bw, a, units, nunits, s);
-    case F32: return units_bw<float>(bw, a, units, nunits, s);
-    case BF16: return units_bw<bf16>(bw, a, units, nunits, s);
+    case F64: return units_bw<double>(bw, nb, a, first, count, s);
+    case F32: return units_bw<float>(bw, nb, a, first, count, s);
+    case BF16: return units_bw<bf16>(bw, nb, a, first, count, s);
     default: return hipErrorInvalidValue;
     }
 }

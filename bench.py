@@ -328,8 +328,8 @@ def bench_ch(torch, b, wl, n, steps, warmup):
     sec, _ = time_loop(torch, lambda: b.mxs_ch_step(p, 1, True), steps, warmup)
     m = b.mxs_ch_mass(p)[0]
     forms = {}
-    # every step form the grid allows, each graph-replayed (the persistent
-    # one for rows of at most 1024 elements)
+    # every step form the grid allows (the persistent one for rows of at most
+    # 1024 elements)
     modes = (((b.MXS_CH_PERSISTENT, "persistent"),) if n <= 1024 else ()) + \
         ((b.MXS_CH_FUSED, "fused"), (b.MXS_CH_SEPARATE, "separate"))
     for mode, key in modes:
@@ -348,7 +348,7 @@ def bench_ch(torch, b, wl, n, steps, warmup):
 
 def bench_ensemble(torch, b, wl, steps, warmup):
     """64 grids of sizes 256^2..1024^2: FP32 and BF16 storage ensembles (one
-    launch per kernel per step, graph-replayed) against the plain FP64 path,
+    launch per kernel per step) against the plain FP64 path,
     both as an FP64 ensemble and one grid at a time."""
     import math
     sizes = wl.ensemble_sizes()
@@ -366,8 +366,7 @@ def bench_ensemble(torch, b, wl, steps, warmup):
         out[f"ensemble_{name}_layout"] = b.mxs_plan_info(p)
         sec, _ = time_loop(torch, lambda: b.mxs_ch_step(p, 1, True), steps, warmup)
         out[f"ensemble_{name}_steps_per_s"] = steps / sec
-        # every step form, each graph-replayed: one persistent launch per
-        # step, the right-hand side inside the row solves, and the separate
+        # every step form: one persistent launch per step, the right-hand side inside the row solves, and the separate
         # launches
         for mode, key in ((b.MXS_CH_PERSISTENT, "persistent"), (b.MXS_CH_FUSED, "fused"),
                           (b.MXS_CH_SEPARATE, "separate")):

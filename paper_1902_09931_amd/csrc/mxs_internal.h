@@ -42,8 +42,9 @@ __device__ __forceinline__ float bf16_to_float(uint16_t b) {
 
 // float -> bfloat16, round to nearest, ties to even; NaN stays NaN.  One
 // conversion instruction for two values (it was 8 integer instructions per
-// value, which bounded the bfloat16 stencils: the 5-point x stencil of an
-// 8192^2 grid 80 -> 57 us); equal to the integer form for every float.
+// value: the tuned 5-point x stencil of an 8192^2 grid 80 -> 76 us, and 59 us
+// in the block form, where the conversions were most of the arithmetic);
+// equal to the integer form for every float.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t floats_to_bf16x2(float lo, float hi) {

@@ -14,7 +14,6 @@ namespace mxs {
 
 namespace {
 
-
 struct WenoPlan final : mxs_plan_s {
     WenoArgs a{};
     int threads = 256;
@@ -62,14 +61,16 @@ struct WenoPlan final : mxs_plan_s {
             double t;
         };
         std::vector<Cand> cands;
-        // one row per workgroup, or one wavefront, only where larger tiles leave CUs without work
+        // grids that leave CUs without work at larger tiles: 1 or 4 rows, down to
+        // one wavefront (they read mostly from cache, so the order of the tiles
+        // is left alone); others: 4 or 8 rows, 256 or 128 threads, both orders
         const bool few = static_cast<long long>(a.nx) * a.ny < 2048LL * 4 * device_cu_count();
-        for (int rows : {1, 4, 8})
+        for (int rows : {few ? 1 : 4, few ? 4 : 8})
             for (int nthreads : {256, 128, 64})
-                if (few || (rows > 1 && nthreads > 64))
                 for (int order : {1, 0})
                     for (int nt : {1, 0})
-                        if (weno_lds_bytes(rows, nthreads) <= static_cast<size_t>(device_lds_limit()))
+                        if ((few ? order == 1 : nthreads > 64) &&
+                            weno_lds_bytes(rows, nthreads) <= static_cast<size_t>(device_lds_limit()))
                             cands.push_back({rows, order, nthreads, nt, 1e30});
         const Cand start{a.rows, a.order, threads, a.nt_store, 0};
         const size_t data = 4 * grid_bytes(a.nx, a.ny, a.ld, F64);

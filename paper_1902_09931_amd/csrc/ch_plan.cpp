@@ -90,6 +90,7 @@ struct CHPlan final : mxs_plan_s {
     DevBuf partial;
     double *mass_host = nullptr;   // pinned: a mass per instance, then the 3 sums of the diagnostics
     int bgroups = 16;   // phase B threads per column
+    int max_nseg = 0;   // segments of the longest column
     int rhs_blocks = 0, rhs_rows = 16, rhs_threads = kRhsThreads, row_lines = 0, row_grid = 1, row_nw = 1, colsAC = 0, colsB = 0,
         mass_blocks = 0, max_nx = 0;
     size_t row_lds = 0;
@@ -225,7 +226,8 @@ struct CHPlan final : mxs_plan_s {
                 return launch_strips(wdtype, dtype, 2, 1, strips, static_cast<const StripInst *>(strip_d[r].ptr),
                                      map_of(strip_map), strip_blocks, s);
             return launch_cols(wdtype, dtype, 2, 1, static_cast<const ColsInst *>(cols_d[r].ptr),
-                               map_of(colsAC_map), map_of(colsB_map), colsAC, colsB, bgroups, s);
+                               map_of(colsAC_map), map_of(colsB_map), colsAC, colsB, bgroups,
+                               max_nseg, s);
         }
         hipError_t e = launch_ch_rhs(dtype, static_cast<const RhsInst *>(rhs_d[r].ptr),
                                      map_of(rhs_map), rhs_blocks, rhs_threads, s);
@@ -237,7 +239,8 @@ struct CHPlan final : mxs_plan_s {
                                  row_ranges[q].count, s);
         if (e != hipSuccess) return e;
         return launch_cols(wdtype, dtype, 2, 1, static_cast<const ColsInst *>(cols_d[r].ptr),
-                           map_of(colsAC_map), map_of(colsB_map), colsAC, colsB, bgroups, s);
+                           map_of(colsAC_map), map_of(colsB_map), colsAC, colsB, bgroups,
+                               max_nseg, s);
     }
 
     hipError_t capture(int r) {
@@ -591,7 +594,10 @@ struct CHPlan final : mxs_plan_s {
         {
             // phase B threads per column from the mean number of segments
             long long segs = 0;
-            for (const Inst &I : inst) segs += (I.ny + kSeg - 1) / kSeg;
+            for (const Inst &I : inst) {
+                segs += (I.ny + kSeg - 1) / kSeg;
+                max_nseg = std::max(max_nseg, (I.ny + kSeg - 1) / kSeg);
+            }
             bgroups = cols_b_groups(static_cast<int>(segs / n));
         }
         const int bcols = cols_b_cols(bgroups);

@@ -165,14 +165,17 @@ __device__ __forceinline__ void cols_a_block(const ColsInst *__restrict__ inst, 
 // thread has at most PB segments, all four words of each are loaded once and
 // kept in registers through both recurrences (one round of loads instead of
 // four, the same arithmetic in the same order).  REG = false keeps the
-// batched loads only (for kernels that have no registers to spare).
-constexpr int PB = 8;
-
+// batched loads only (for kernels that have no registers to spare).  Bound by
+// the latency of one wavefront's loads and by its serial chain.  Pentadiagonal
+// FP64 column solves with PB = 8 and, for more than 128 segments, 16: 222 x
+// 7278 31.1 / 24.7 us, 700 x 5000 34.0 / 29.5, 2051 x 8192 123 / 114.5, 8192^2
+// 377 / 358; with 128 segments or fewer 16 is slower (2051 x 3000 44.6 / 45.5).
+// 32 threads per column, 8 segments each: 222 x 7278 24.3, 2051 x 8192 129.
 __device__ __forceinline__ void mat2_load(const double *m, Aff &x) {
     x.a = m[0]; x.b = m[1]; x.c = m[2]; x.d = m[3];
 }
 
-template <int BW, int G, bool REG = true>
+template <int BW, int G, bool REG = true, int PB = 8>
 __device__ __forceinline__ void cols_b_block(const ColsInst *__restrict__ inst, const int *__restrict__ map,
                                              const int blk, Aff *xa) {
     constexpr int kBCols = kColsThreads / G;
@@ -221,7 +224,7 @@ __device__ __forceinline__ void cols_b_block(const ColsInst *__restrict__ inst, 
         xa[q * kBCols + cl] = m;
         __syncthreads();
         Aff pre = aff_identity(), tot = aff_identity();
-#pragma unroll
+#pragma unroll 4
         for (int r = 0; r < G; ++r) {
             const Aff x = xa[r * kBCols + cl];
             if (r < q) pre = compose_x(x, pre);
@@ -266,7 +269,7 @@ __device__ __forceinline__ void cols_b_block(const ColsInst *__restrict__ inst, 
         __syncthreads();
         pre = aff_identity();
         tot = aff_identity();
-#pragma unroll
+#pragma unroll 4
         for (int r = G - 1; r >= 0; --r) {
             const Aff x = xa[r * kBCols + cl];
             if (r > q) pre = compose_x(x, pre);

@@ -177,6 +177,6 @@ hipError_t launch_wave_rows(int dtype, int bw, int nb, const RowsInst *inst, con
 // (rhs dtype, output dtype) pairs: (F64,F64), (F32,F32), (BF16,BF16), (F32,BF16).
 hipError_t launch_cols(int rhs_dtype, int x_dtype, int bw, int epilogue, const ColsInst *inst,
                        const int *mapAC, const int *mapB, int blocksAC, int blocksB, int bgroups,
-                       hipStream_t s);
+                       int max_nseg, hipStream_t s);
 
 }  // namespace mxs

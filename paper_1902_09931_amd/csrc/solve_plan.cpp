@@ -125,7 +125,7 @@ struct SolvePlan final : mxs_plan_s {
                               blocksAC, s);
         } else {
             e = launch_cols(dtype, dtype, bw, 0, static_cast<const ColsInst *>(tables[cur].ptr), nullptr,
-                            nullptr, blocksAC, blocksB, bgroups, s);
+                            nullptr, blocksAC, blocksB, bgroups, cols.nseg, s);
         }
         return e == hipSuccess ? MXS_OK : hip_fail(e, "cyclic solve launch");
     }

@@ -52,6 +52,24 @@ def test_column_strips_match_oracle(nx, ny, coef, dt):
         assert np.array_equal(got[:, nx:], r[:, nx:] if in_place else np.full((ny, 3), 7.0))
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("coef", [TRI, PENTA], ids=["tri", "penta"])
+@pytest.mark.parametrize("nx,ny", [(33, 4096), (17, 4097), (5, 4128), (40, 7278), (16, 8191), (3, 8192), (18, 8193)])
+def test_tall_columns_match_oracle(nx, ny, coef, dt):
+    """Columns of 128, 129, 256 and 257 segments: phase B with 8 or 16
+    segments per thread in registers, or neither; same bound as above."""
+    rng = np.random.default_rng(ny)
+    r = round_to(rng.uniform(-1, 1, (ny, nx)), dt)
+    ref = oracle.cyclic_solve_grid(oracle.circulant_bands(coef), 0, r)
+    rhs = to_device(r, dt)
+    x = torch.empty_like(rhs)
+    p = b.mxs_create_cyclic_solve(len(coef) - 1, coef, b.MXS_LINES_COLS, nx, ny, nx, None, code(dt), rhs, x)
+    b.mxs_compute(p)
+    torch.cuda.synchronize()
+    b.mxs_destroy(p)
+    assert np.all(np.abs(x.double().cpu().numpy() - ref) <= 1e-12 * np.abs(ref).max() + US[dt] * np.abs(ref))
+
+
 # (ny, nx) of one ensemble per entry: strips of every shape, several
 # instances of different heights in one launch, rows of every length class of
 # the quad kernel with full and partial last quads, lanes and wavefronts, row

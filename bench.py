@@ -42,7 +42,7 @@ TRAFFIC_SOURCES = ["paper_1902_09931_amd/csrc/stencil2d.hip", "paper_1902_09931_
 # autotuner's choices for the 8192^2 FP64 set; the 3x3 kernels have been
 # tuned to 128 or 256 threads, with or without lane-shift x exchange.
 _L33 = "6,1,256,1,8|6,1,128,1,8|6,1,256,1,8,1|6,1,128,1,8,1"
-PROFILE_LAYOUTS = f"x=4,1,256,1;y=4,1,256,1,8;xy={_L33};fun={_L33}"
+PROFILE_LAYOUTS = f"x=4,1,256,1|4,1,256,1,4,1;y=4,1,256,1,8|12,1,256,1,16;xy={_L33};fun={_L33}"
 METRIC = "stencil Gpoints/s + % HBM peak; CH ADI steps/s (FP64 vs FP32/batched)"
 # The paper's own serial-versus-GPU figures (Sec. 5.4), for context only: a
 # different machine and a different program (its whole ADI Cahn-Hilliard code).

@@ -92,7 +92,7 @@ __device__ __forceinline__ double weno5(double v1, double v2, double v3, double 
 // for a positive velocity, f[6..1] (in that order) otherwise, where the
 // one-sided differences are those of the reversed values with the sign
 // changed.  The combination is homogeneous of degree one, so spacing and sign
-// go into the velocity instead of five differences (8192^2 untuned 565 -> 513
+// go into the velocity instead of five differences (8192^2 untuned 580 -> 513
 // us).
 __device__ __forceinline__ double weno_upwind(const double (&g)[6], const WenoConst &K) {
     return weno5(g[1] - g[0], g[2] - g[1], g[3] - g[2], g[4] - g[3], g[5] - g[4], K);

@@ -156,6 +156,27 @@ def test_fused_replays_with_strips_equal_eager_steps():
     assert rel_err(runs[0][-1].cpu().numpy(), runs[1][-1].cpu().numpy()) == 0.0
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("ny", [4096, 4097, 6000, 8193])
+def test_tall_separate_and_persistent_steps_are_equal(ny, dt):
+    """Phase B keeps 8, 16 or no segments per thread in registers in the
+    separate form and none in the persistent one: the states are the same bit
+    for bit."""
+    nx = 40
+    c0 = wl.ch_initial(ny, nx, seed=6)
+    h = 2 * math.pi / nx
+    runs = []
+    for mode in (b.MXS_CH_SEPARATE, b.MXS_CH_PERSISTENT):
+        q = [to_device(c0, dt), to_device(c0, dt), torch.zeros((ny, nx), dtype=TORCH[dt], device="cuda")]
+        p = b.mxs_ch_create(nx, ny, h, h, 0.1 * h * h, 1.0, 0.01, code(dt), *q)
+        b.mxs_ch_set_step_mode(p, mode)
+        b.mxs_ch_step(p, 4, False)
+        b.mxs_ch_mass(p)
+        b.mxs_destroy(p)
+        runs.append(torch.stack(q))
+    assert torch.equal(*runs)
+
+
 def test_default_stream_is_torchs_current_stream():
     """Calls without a stream run on torch's current one, inside and outside
     a stream context."""

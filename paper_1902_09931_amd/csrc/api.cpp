@@ -258,7 +258,7 @@ struct Stencil2DPlan final : mxs_plan_s {
 // ---------------------------------------------------------------------------
 struct Stencil1DPlan final : mxs_plan_s {
     Stencil1DArgs a{};
-    int dtype = F64, nwx = 1, threads = 256, grid = 1;
+    int dtype = F64, threads = 256, grid = 1;
     DevBuf wts, offsets, tile_first;
     Stencil1DPlan() : mxs_plan_s(KIND_STENCIL1D) {}
 
@@ -272,7 +272,7 @@ struct Stencil1DPlan final : mxs_plan_s {
         return MXS_OK;
     }
     mxs_status compute(hipStream_t s) override {
-        hipError_t e = launch_stencil1d(dtype, nwx, a, threads, grid, s);
+        hipError_t e = launch_stencil1d(dtype, a, threads, grid, s);
         return e == hipSuccess ? MXS_OK : hip_fail(e, "stencil1d launch");
     }
     mxs_status swap() override {
@@ -485,8 +485,9 @@ mxs_status mxs_create_1d_batch(int nbatch, const long long *offsets, int bc, int
     if (!weights) return fail(MXS_ERR_INVALID_ARG, "weights is NULL");
     mxs_status st = check_coe(coe, ncoe);
     if (st) return st;
-    const int nwx = bucket_width(left + right + 1);
-    if (!nwx) return fail(MXS_ERR_UNSUPPORTED, "window of %d taps is too wide", left + right + 1);
+    if (left > kMaxTaps1D || right > kMaxTaps1D || left + right + 1 > kMaxTaps1D)
+        return fail(MXS_ERR_UNSUPPORTED, "window is wider than %d taps", kMaxTaps1D);
+    const int taps = left + right + 1;
     if (offsets[0] != 0) return fail(MXS_ERR_INVALID_ARG, "offsets[0] must be 0");
     for (int b = 0; b < nbatch; ++b)
         if (offsets[b + 1] - offsets[b] <= left + right)
@@ -498,7 +499,6 @@ mxs_status mxs_create_1d_batch(int nbatch, const long long *offsets, int bc, int
     Stencil1DPlan *p = new (std::nothrow) Stencil1DPlan();
     if (!p) return fail(MXS_ERR_OOM, "host allocation failed");
     p->dtype = dtype;
-    p->nwx = nwx;
     p->a.total = total;
     p->a.nbatch = nbatch;
     p->a.L = left;
@@ -531,7 +531,7 @@ mxs_status mxs_create_1d_batch(int nbatch, const long long *offsets, int bc, int
         if (t > 0) maxsig = std::max(maxsig, tf[t] - tf[t - 1] + 2);
     }
     p->a.max_sig_per_tile = std::max(maxsig, 2);
-    if (stencil1d_lds_bytes(dtype, nwx, p->threads, p->a.max_sig_per_tile, p->a.vecs) >
+    if (stencil1d_lds_bytes(dtype, taps, p->threads, p->a.max_sig_per_tile, p->a.vecs) >
         static_cast<size_t>(device_lds_limit())) {
         delete p;
         return fail(MXS_ERR_UNSUPPORTED, "signals too short for the LDS budget");
@@ -539,7 +539,7 @@ mxs_status mxs_create_1d_batch(int nbatch, const long long *offsets, int bc, int
     hipError_t e;
     if ((e = p->offsets.upload(offsets, sizeof(long long) * (nbatch + 1))) != hipSuccess ||
         (e = p->tile_first.upload(tf.data(), sizeof(int) * tf.size())) != hipSuccess ||
-        (e = upload_weights(p->wts, weights, left, right, 0, 0, nwx, 1, dtype)) != hipSuccess) {
+        (e = upload_weights(p->wts, weights, left, right, 0, 0, taps, 1, dtype)) != hipSuccess) {
         delete p;
         return hip_fail(e, "batch tables upload");
     }

@@ -233,19 +233,23 @@ struct Stencil1DArgs {
     int L, R;
     int periodic;
     int ncoe;
-    const void *wts;            // device, NWX padded weights
+    const void *wts;            // device, L + R + 1 weights
     double coe_d[kMaxCoe];
     float coe_f[kMaxCoe];
     int max_sig_per_tile;       // LDS slots reserved for offsets
 };
 
-// Window buckets: padded widths the kernels are compiled for.
+// Window buckets: padded widths the 2D kernels are compiled for.
 int bucket_width(int taps);   // 1, 3, 5, 9 or 17; 0 if too wide
+// Most taps of a 1D window; the 1D kernels are compiled for every number of taps.
+constexpr int kMaxTaps1D = 17;
 
 hipError_t launch_stencil2d(int dtype, int nwx, int nwy, const Stencil2DArgs &a,
                             int threads, hipStream_t s);
-hipError_t launch_stencil1d(int dtype, int nwx, const Stencil1DArgs &a, int threads,
-                            int grid, hipStream_t s);
+hipError_t launch_stencil1d(int dtype, const Stencil1DArgs &a, int threads, int grid, hipStream_t s);
+hipError_t launch_stencil1d_f64(const Stencil1DArgs &a, int threads, int grid, hipStream_t s);
+hipError_t launch_stencil1d_f32(const Stencil1DArgs &a, int threads, int grid, hipStream_t s);
+hipError_t launch_stencil1d_bf16(const Stencil1DArgs &a, int threads, int grid, hipStream_t s);
 size_t stencil2d_lds_bytes(int dtype, int nwx, int nwy, int threads, int block_rows, int xshuffle);
 // Read `bytes` (a multiple of 16) of a device buffer once, so that the
 // memory-side cache holds none of the data timed next.
@@ -261,6 +265,6 @@ bool stencil2d_block_ok(int dtype, int nwx, int nwy, int block_rows);
 // (centred windows of padded width nwx, at most one vector on each side);
 // windows along x alone have this form of it only.
 bool stencil2d_xshuffle_ok(int dtype, int nwx, int nwy, int left, int right, int block_rows);
-size_t stencil1d_lds_bytes(int dtype, int nwx, int threads, int max_sig, int vecs);
+size_t stencil1d_lds_bytes(int dtype, int taps, int threads, int max_sig, int vecs);
 
 }  // namespace mxs

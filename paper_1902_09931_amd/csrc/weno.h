@@ -12,7 +12,8 @@ struct WenoArgs {
     long long ld;
     int nx, ny;
     double rdx, rdy;           // 1 / dx, 1 / dy
-    int rows;                  // output rows per workgroup (4 or 8)
+    double floor_x, floor_y;   // the weights' floor 1e-99 times dx^2 and dy^2
+    int rows;                  // output rows per workgroup (1, 4 or 8)
     int nchunks, nstrips;
     int order;                 // tile order, as for the 2D stencils
     int nt_store;              // non-temporal output stores

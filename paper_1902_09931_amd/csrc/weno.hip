@@ -30,7 +30,8 @@ constexpr int kWenoPad = 4;   // halo columns staged on each side (3 used), a wh
 // three third-order ENO candidates, their smoothness indicators s_k, and the
 // nonlinear weights w_k = a_k / sum a, a_k = g_k / (s_k + eps)^2 with the
 // optimal weights g = 1/10, 6/10, 3/10 and eps = 1e-6 times the largest
-// squared difference plus 1e-99.
+// squared difference plus `floor` (1e-99 for the differences divided by the
+// spacing).
 //
 // Arithmetic: the candidates by multiplications with rounded constants
 // instead of divisions, and the weights with one quotient instead of four:
@@ -43,16 +44,17 @@ constexpr int kWenoPad = 4;   // halo columns staged on each side (3 used), a wh
 // The constants live in scalar registers (WenoConst): written as literals, the
 // compiler moved their halves into vector registers at every use.
 struct WenoConst {
-    double third, sixth, m76, c116, c56, c1312, e6, e99, g1, g2, g3;
+    double third, sixth, m76, c116, c56, c1312, e6, g1, g2, g3;
     __device__ __forceinline__ WenoConst()
         : third(1.0 / 3.0), sixth(1.0 / 6.0), m76(-7.0 / 6.0), c116(11.0 / 6.0), c56(5.0 / 6.0), c1312(13.0 / 12.0),
-          e6(1e-6), e99(1e-99), g1(0.1), g2(0.6), g3(0.3) {
+          e6(1e-6), g1(0.1), g2(0.6), g3(0.3) {
         asm("" : "+s"(third), "+s"(sixth), "+s"(m76), "+s"(c116), "+s"(c56), "+s"(c1312));
-        asm("" : "+s"(e6), "+s"(e99), "+s"(g1), "+s"(g2), "+s"(g3));
+        asm("" : "+s"(e6), "+s"(g1), "+s"(g2), "+s"(g3));
     }
 };
 
-__device__ __forceinline__ double weno5(double v1, double v2, double v3, double v4, double v5, const WenoConst &K) {
+__device__ __forceinline__ double weno5(double v1, double v2, double v3, double v4, double v5, const double floor,
+                                        const WenoConst &K) {
     const double p1 = fma(v1, K.third, fma(v2, K.m76, v3 * K.c116));
     const double p2 = fma(v2, -K.sixth, fma(v3, K.c56, v4 * K.third));
     const double p3 = fma(v3, K.third, fma(v4, K.c56, v5 * -K.sixth));
@@ -67,7 +69,7 @@ __device__ __forceinline__ double weno5(double v1, double v2, double v3, double 
     // the largest square is the square of the largest magnitude (rounding
     // of a square is monotone in |v|), one multiplication instead of five
     const double va = fmax(fmax(fmax(fabs(v1), fabs(v2)), fmax(fabs(v3), fabs(v4))), fabs(v5));
-    const double eps = fma(K.e6, va * va, K.e99);
+    const double eps = fma(K.e6, va * va, floor);
     double d1 = s1 + eps, d2 = s2 + eps, d3 = s3 + eps;
     const int ex = __builtin_amdgcn_frexp_exp(fmax(fmax(d1, d2), d3));
     d1 = __builtin_amdgcn_ldexp(d1, -ex);
@@ -91,11 +93,12 @@ __device__ __forceinline__ double weno5(double v1, double v2, double v3, double 
 // it reads, in upwind order: f[0..5] of the seven values around the point f[3]
 // for a positive velocity, f[6..1] (in that order) otherwise, where the
 // one-sided differences are those of the reversed values with the sign
-// changed.  The combination is homogeneous of degree one, so spacing and sign
-// go into the velocity instead of five differences (8192^2 untuned 580 -> 513
-// us).
-__device__ __forceinline__ double weno_upwind(const double (&g)[6], const WenoConst &K) {
-    return weno5(g[1] - g[0], g[2] - g[1], g[3] - g[2], g[4] - g[3], g[5] - g[4], K);
+// changed.  With the floor of the weights scaled by the spacing squared the
+// combination is homogeneous of degree one in the differences, so the spacing
+// is divided out of the result instead of five differences (8192^2 untuned
+// 580 -> 513 us), and the sign goes into the velocity.
+__device__ __forceinline__ double weno_upwind(const double (&g)[6], const double floor, const WenoConst &K) {
+    return weno5(g[1] - g[0], g[2] - g[1], g[3] - g[2], g[4] - g[3], g[5] - g[4], floor, K);
 }
 
 template <int ROWS>
@@ -205,8 +208,8 @@ __global__ void __launch_bounds__(256) weno_adv_kernel(const WenoArgs a) {
                 gx[m] = lp[st * (m - 3)];
                 gy[m] = pv ? f[k + m][q] : f[k + 6 - m][q];
             }
-            const double px = weno_upwind(gx, K), py = weno_upwind(gy, K);
-            res[q] = fma(fabs(u[k][q]) * rdx, px, fabs(v[k][q]) * rdy * py);
+            const double px = weno_upwind(gx, a.floor_x, K) * rdx, py = weno_upwind(gy, a.floor_y, K) * rdy;
+            res[q] = fma(fabs(u[k][q]), px, fabs(v[k][q]) * py);
         }
         const gptr<double> rowp = out + static_cast<long long>(j0 + k) * a.ld;
         if (clean && ib >= lo) {

@@ -129,6 +129,10 @@ mxs_status mxs_create_weno_adv(int nx, int ny, long long ld, double dx, double d
     p->a.ld = ld;
     p->a.rdx = 1.0 / dx;
     p->a.rdy = 1.0 / dy;
+    // (a normal number whatever the spacing: the weights divide by it)
+    auto weight_floor = [](double h) { return std::min(std::max(1e-99 * h * h, 1e-300), 1e300); };
+    p->a.floor_x = weight_floor(dx);
+    p->a.floor_y = weight_floor(dy);
     p->a.u = u;
     p->a.v = v;
     mxs_status st = p->set_io(phi, out);

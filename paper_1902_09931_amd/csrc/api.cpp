@@ -216,10 +216,12 @@ struct Stencil2DPlan final : mxs_plan_s {
         }
     }
 
+    // Plans that share a tuned layout.  Whether the window is centred belongs to
+    // it: only centred ones can take their x neighbours from lanes.
     std::string key() const {
         char buf[160];
-        snprintf(buf, sizeof buf, "s2d:%d:%d:%d:%d:%d:%lld:%d:%d", dtype, nwx, nwy, a.nx, a.ny, a.ld,
-                 a.periodic, a.ncoe > 0);
+        snprintf(buf, sizeof buf, "s2d:%d:%d:%d:%d:%d:%lld:%d:%d:%d", dtype, nwx, nwy, a.nx, a.ny, a.ld,
+                 a.periodic, a.ncoe > 0, a.L == nwx / 2 && a.R == nwx / 2);
         return buf;
     }
 

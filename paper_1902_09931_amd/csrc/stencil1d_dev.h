@@ -244,10 +244,15 @@ __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
 
 template <typename T, int TAPS>
 hipError_t launch_one(const Stencil1DArgs &a, int threads, int grid, hipStream_t s) {
-    const size_t lds = stencil1d_lds_bytes(std::is_same<T, double>::value ? F64
+    size_t lds = stencil1d_lds_bytes(std::is_same<T, double>::value ? F64
                                            : std::is_same<T, float>::value ? F32 : BF16,
                                            TAPS, threads, a.max_sig_per_tile, a.vecs);
     if (a.vecs != kS1dVecs && a.vecs != 1) return hipErrorInvalidValue;
+    // Two taps in double are so little work that 8 workgroups per CU get into
+    // each other's way in memory: 65,536 signals of 64 .. 4096 take 374 us with
+    // 8 or 9, 355 with 6, and 4 cost short signals (500,000 of 20 .. 40: 52, 54,
+    // 60 us).
+    if (sizeof(T) == 8 && TAPS == 2 && a.vecs == kS1dVecs) lds = lds > 26 * 1024 ? lds : 26 * 1024;
     const dim3 g(grid), b(threads);
     if (a.vecs == kS1dVecs && a.periodic)
         hipLaunchKernelGGL((stencil1d_kernel<T, TAPS, kS1dVecs, true>), g, b, lds, s, a);

@@ -82,6 +82,16 @@ __global__ void __launch_bounds__(64) wave_rows_kernel(const RowsInst *__restric
     wave_line<T, BW, NB>(RowsSrc<T>{inst, map}, first + k, stage);
 }
 
+// A launch holds fewer than 2^32 threads and is cut off without an error beyond,
+// so more lines than this go out in several.
+constexpr int kLinesPerLaunch = 1 << 25;
+template <class Launch> hipError_t in_pieces(int first, int count, Launch launch) {
+    hipError_t e = hipSuccess;
+    for (long long k = 0; k < count && e == hipSuccess; k += kLinesPerLaunch)
+        e = launch(static_cast<int>(first + k), static_cast<int>(count - k < kLinesPerLaunch ? count - k : kLinesPerLaunch));
+    return e;
+}
+
 template <typename T>
 hipError_t units_bw(int bw, int nb, const RaggedLines &a, int first, int count, hipStream_t s) {
     const dim3 grid(count), block(64);
@@ -135,37 +145,40 @@ hipError_t rows_bw(int bw, int nb, const RowsInst *inst, const int *map, int fir
 
 hipError_t launch_wave_units(int dtype, int bw, int nb, const RaggedLines &a, int first, int count,
                              hipStream_t s) {
-    if (count <= 0) return hipSuccess;
     if (bw != 1 && bw != 2) return hipErrorInvalidValue;
-    switch (dtype) {
-    case F64: return units_bw<double>(bw, nb, a, first, count, s);
-    case F32: return units_bw<float>(bw, nb, a, first, count, s);
-    case BF16: return units_bw<bf16>(bw, nb, a, first, count, s);
-    default: return hipErrorInvalidValue;
-    }
+    return in_pieces(first, count, [&](int k, int n) {
+        switch (dtype) {
+        case F64: return units_bw<double>(bw, nb, a, k, n, s);
+        case F32: return units_bw<float>(bw, nb, a, k, n, s);
+        case BF16: return units_bw<bf16>(bw, nb, a, k, n, s);
+        default: return hipErrorInvalidValue;
+        }
+    });
 }
 
 hipError_t launch_wave_ragged(int dtype, int bw, int nb, const RaggedLines &a, int first, int count,
                               hipStream_t s) {
-    if (count <= 0) return hipSuccess;
     if (bw != 1 && bw != 2) return hipErrorInvalidValue;
-    switch (dtype) {
-    case F64: return bw == 2 ? ragged_nb<double, 2>(nb, a, first, count, s) : ragged_nb<double, 1>(nb, a, first, count, s);
-    case F32: return bw == 2 ? ragged_nb<float, 2>(nb, a, first, count, s) : ragged_nb<float, 1>(nb, a, first, count, s);
-    case BF16: return bw == 2 ? ragged_nb<bf16, 2>(nb, a, first, count, s) : ragged_nb<bf16, 1>(nb, a, first, count, s);
-    default: return hipErrorInvalidValue;
-    }
+    return in_pieces(first, count, [&](int k, int n) {
+        switch (dtype) {
+        case F64: return bw == 2 ? ragged_nb<double, 2>(nb, a, k, n, s) : ragged_nb<double, 1>(nb, a, k, n, s);
+        case F32: return bw == 2 ? ragged_nb<float, 2>(nb, a, k, n, s) : ragged_nb<float, 1>(nb, a, k, n, s);
+        case BF16: return bw == 2 ? ragged_nb<bf16, 2>(nb, a, k, n, s) : ragged_nb<bf16, 1>(nb, a, k, n, s);
+        default: return hipErrorInvalidValue;
+        }
+    });
 }
 
 hipError_t launch_wave_rows(int dtype, int bw, int nb, const RowsInst *inst, const int *map, int first,
                             int count, hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    switch (dtype) {
-    case F64: return rows_bw<double>(bw, nb, inst, map, first, count, s);
-    case F32: return rows_bw<float>(bw, nb, inst, map, first, count, s);
-    case BF16: return rows_bw<bf16>(bw, nb, inst, map, first, count, s);
-    default: return hipErrorInvalidValue;
-    }
+    return in_pieces(first, count, [&](int k, int n) {
+        switch (dtype) {
+        case F64: return rows_bw<double>(bw, nb, inst, map, k, n, s);
+        case F32: return rows_bw<float>(bw, nb, inst, map, k, n, s);
+        case BF16: return rows_bw<bf16>(bw, nb, inst, map, k, n, s);
+        default: return hipErrorInvalidValue;
+        }
+    });
 }
 
 }  // namespace mxs

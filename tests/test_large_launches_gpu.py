@@ -1,0 +1,52 @@
+"""Calls of so many lines, columns or tiles that one launch cannot hold a
+workgroup for each: a launch holds fewer than 2^32 threads and is cut off without
+an error beyond that."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import torch
+
+pytestmark = pytest.mark.gpu
+
+b = pytest.importorskip("paper_1902_09931_amd.binding")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+TRI = [2.5, -1.0]
+# inverse of circ(-1, 2.5, -1) of three elements
+INV3 = np.linalg.inv(np.array([[2.5, -1, -1], [-1, 2.5, -1], [-1, -1, 2.5]]))
+
+
+def fill(shape, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.empty(shape, dtype=torch.float32, device="cuda").uniform_(-1, 1, generator=gen)
+
+
+def check(x, r, dim):
+    """x against INV3 r along dim (three elements) in double, in pieces: 1e-12 of
+    max |x| and one rounding to float."""
+    inv = torch.from_numpy(INV3).cuda()
+    n = r.shape[1 - dim]
+    for k in range(0, n, 1 << 24):
+        xs, rs = (v.narrow(1 - dim, k, min(1 << 24, n - k)).double() for v in (x, r))
+        ref = rs @ inv if dim == 1 else inv @ rs
+        assert bool((xs - ref).abs().le(1e-12 * 2 + 2.0 ** -24 * ref.abs()).all()), k
+
+
+@pytest.mark.parametrize("form", ["classes", "units", "rows"])
+def test_lines_beyond_one_launch(monkeypatch, form):
+    n = (1 << 26) + 3
+    r = fill((n, 3), 71)
+    x = torch.zeros_like(r)
+    if form == "rows":
+        p = b.mxs_create_cyclic_solve(1, TRI, b.MXS_LINES_ROWS, 3, n, 3, None, b.MXS_F32, r, x)
+    else:
+        monkeypatch.setenv("MXS_RAGGED_FORM", form)
+        p = b.mxs_create_cyclic_solve(1, TRI, b.MXS_LINES_RAGGED, 0, 0, 0, np.arange(n + 1, dtype=np.int64) * 3,
+                                      b.MXS_F32, r, x)
+    try:
+        b.mxs_compute(p)
+        torch.cuda.synchronize()
+    finally:
+        b.mxs_destroy(p)
+    check(x, r, 1)

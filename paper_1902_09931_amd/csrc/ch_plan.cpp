@@ -602,12 +602,13 @@ struct CHPlan final : mxs_plan_s {
         }
         const int bcols = cols_b_cols(bgroups);
         int max_ny = 0;
-        long long sum_nx = 0;
+        long long sum_nx = 0, points = 0;
         for (const Inst &I : inst) {
             max_ny = std::max(max_ny, I.ny);
             sum_nx += I.nx;
+            points += static_cast<long long>(I.nx) * I.ny;
         }
-        strips = reg_rows && max_ny > 2 * kSeg ? strip_shape_for(max_ny, sum_nx, 1) : -1;
+        strips = reg_rows && max_ny > 2 * kSeg ? strip_shape_for(max_ny, sum_nx, points, dtype, 2, 1) : -1;
         const size_t stab = strips >= 0 ? strip_tab_size(strips) : 0;
         std::vector<double> st(stab * n);
         std::vector<StripInst> strip_h(strips >= 0 ? n : 0);

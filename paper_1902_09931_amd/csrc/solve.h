@@ -142,9 +142,10 @@ void fill_strip_tab(const CyclicFactor &f, int bw, int ny, int L, int spw, int n
 struct StripShape {
     int threads, columns, rows;
 };
-// The shape for columns of at most ny_max rows, sum_nx columns in all, or -1
-// where the three phases are the better choice (epilogue as in launch_cols).
-int strip_shape_for(int ny_max, long long sum_nx, int epilogue);
+// The shape for columns of at most ny_max rows, sum_nx columns and `points`
+// values in all, or -1 where the three phases are the better choice (x_dtype,
+// bw and epilogue as in launch_cols).
+int strip_shape_for(int ny_max, long long sum_nx, long long points, int x_dtype, int bw, int epilogue);
 StripShape strip_shape(int shape);
 size_t strip_tab_size(int shape);   // doubles in the power table of one instance
 // Fill the coefficients of an instance (not its pointers, pitch, table

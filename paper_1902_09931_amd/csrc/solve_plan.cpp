@@ -366,7 +366,7 @@ extern "C" mxs_status mxs_create_cyclic_solve(int bw, const double *coef, int ge
             p->nmax = nx;
             if (nx <= kWaveLineMax && !force_lds_lines()) p->wave.push_back({wave_nb(nx), 0, ny});
             p->set_waves(line_waves(nx));
-        } else if ((p->shape = strip_shape_for(ny, nx, 0)) >= 0) {
+        } else if ((p->shape = strip_shape_for(ny, nx, static_cast<long long>(nx) * ny, dtype, bw, 0)) >= 0) {
             std::vector<double> tab(strip_tab_size(p->shape));
             fill_strip(p->f, bw, nx, ny, p->shape, &p->strip, tab.data());
             p->strip.ld = ld;

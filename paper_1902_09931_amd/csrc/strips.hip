@@ -43,18 +43,68 @@ hipError_t strips_bw(int bw, int shape, const StripInst *inst, const int *map, i
 
 }  // namespace
 
-// Measured on FP64 grids, Cahn-Hilliard update, three phases against strips:
-// 512^2 14.8 / 6.5 us (shape 0), 1024^2 19.0 / 12.4 (1; shape 2: 17), 2500 x
-// 700 27.4 / 17.5 (2; shape 1: 20.5), 8000 x 1000 63.8 / 57.9 (2; shape 1:
-// 90), 3000 x 2000 68.8 / 53.7 (3; shape 4: 57), 1536^2 38.9 / 33.5 (4;
+namespace {
+
+// Most columns for which strips are used instead of the three phases, by the
+// columns' mean rows.  Once the CUs are full a strip of 16 columns takes 10 ns
+// (tridiagonal) or 16 (pentadiagonal) however few rows it has, and moves short
+// pieces of many rows; the phases take about 6 (double), 3.5 (float) or 2.2 ps
+// (bfloat16) per point, but 9 to 12 us for their three launches.  So strips are
+// for few columns, and for many only with rows enough.  Phases / strips, us:
+//   plain solves: pentadiagonal double  4096 columns x 32 rows 10.4 / 8.4,
+//     16384 x 64 11.7 / 20.3, 16384 x 320 31.3 / 25.7, 131072 x 200 145 / 177,
+//     131072 x 400 293 / 220, 10^6 x 8 101 / 981;  tridiagonal float 8192 x 64
+//     9.6 / 7.6, 16384 x 64 9.4 / 12.8, 32768 x 400 41.8 / 33.2;  pentadiagonal
+//     float 8192 x 256 11.9 / 12.4, 16384 x 256 15.7 / 22.4, 32768 x 512 47.7 /
+//     46.8, 32768 x 1200 113 / 165;  pentadiagonal bfloat16 6000 x 64 11.7 / 11.2,
+//     12000 x 256 16.6 / 18.8, 6000 x 1200 35.2 / 39.7
+//   Cahn-Hilliard steps (8192 columns are one round of two workgroups per CU):
+//     float 4 grids of 2048 columns x 40 rows 22.7 / 21.1, 9 of 1024 x 40 19.6 /
+//     22.7;  double 4 of 4096 x 65 31 / 41, x 256 64 / 60, 16 of 4096 x 256 238 /
+//     252, x 400 376 / 353;  float 64 of 256 x 256 34 / 40, of 1024 x 512 235 /
+//     246, of 1024 x 700 335 / 322;  bfloat16 64 of 1024 x 700 280 / 288
+struct ColumnLimit {
+    int rows;            // for columns of fewer rows than this
+    long long columns;
+};
+constexpr long long kAny = 1LL << 40;
+
+long long columns_max(int dtype, int bw, int epilogue, long long rows) {
+    static constexpr ColumnLimit plain[3][2][4] = {
+        {{{200, 10000}, {2049, kAny}}, {{150, 7000}, {320, 10000}, {2049, kAny}}},                  // double
+        {{{150, 10000}, {400, 14000}, {2049, kAny}}, {{150, 5000}, {512, 9000}, {1025, kAny}, {2049, 9000}}},
+        {{{2049, 10000}}, {{1025, 9000}, {2049, 5000}}},                                            // bfloat16
+    };
+    static constexpr ColumnLimit update[3][4] = {
+        {{256, 8192}, {320, 20000}, {2049, kAny}},
+        {{400, 8192}, {600, 20000}, {1025, kAny}, {2049, 8192}},
+        {{600, 8192}, {1025, 20000}, {2049, 8192}},
+    };
+    const ColumnLimit *l = epilogue ? update[dtype] : plain[dtype][bw - 1];
+    for (int k = 0; k < 4; ++k)
+        if (rows < l[k].rows) return l[k].columns;
+    return 0;
+}
+
+}  // namespace
+
+// Shapes, measured on FP64 grids, Cahn-Hilliard update, three phases against
+// strips: 512^2 14.8 / 6.5 us (shape 0), 1024^2 19.0 / 12.4 (1; shape 2: 17),
+// 2500 x 700 27.4 / 17.5 (2; shape 1: 20.5), 8000 x 1000 63.8 / 57.9 (2; shape
+// 1: 90), 3000 x 2000 68.8 / 53.7 (3; shape 4: 57), 1536^2 38.9 / 33.5 (4;
 // shape 3: 40), 2048^2 43.8 / 47.8 (4), 2051 x 3000 75 / 90 (1024 threads of
 // 32 rows, 8 columns).  The plain solve, which has half the words to move,
-// gains more (2048^2 27.6 / 19.2).
-int strip_shape_for(int ny_max, long long sum_nx, int epilogue) {
+// gains more (2048^2 27.6 / 19.2).  From 64 segments on the phases give a
+// column 16 threads instead of 4 in their middle one, and the update of few
+// columns of 2017 .. 2048 rows goes to them (steps of 512 x 2048 double 31.1 /
+// 33.9 us, of 1024 x 2048 float 28.3 / 30.8, double 43.6 / 40.1).
+int strip_shape_for(int ny_max, long long sum_nx, long long points, int x_dtype, int bw, int epilogue) {
+    if (ny_max > 2048 || sum_nx > columns_max(x_dtype, bw, epilogue, points / sum_nx)) return -1;
     if (ny_max <= 1024) return sum_nx >= 2048 ? 2 : ny_max <= 512 ? 0 : 1;
-    if (ny_max > 2048) return -1;
     if (sum_nx >= 2800) return 3;
-    return epilogue == 0 || sum_nx * ny_max <= 3000000 ? 4 : -1;
+    if (epilogue && sum_nx * ny_max > 3000000) return -1;
+    if (epilogue && cols_b_groups((ny_max + kSeg - 1) / kSeg) == 16 && (x_dtype != F64 || sum_nx < 768)) return -1;
+    return 4;
 }
 
 StripShape strip_shape(int shape) {

@@ -50,3 +50,16 @@ def test_lines_beyond_one_launch(monkeypatch, form):
     finally:
         b.mxs_destroy(p)
     check(x, r, 1)
+
+
+def test_columns_beyond_one_launch():
+    nx = (1 << 27) + 5
+    r = fill((3, nx), 73)
+    x = torch.zeros_like(r)
+    p = b.mxs_create_cyclic_solve(1, TRI, b.MXS_LINES_COLS, nx, 3, nx, None, b.MXS_F32, r, x)
+    try:
+        b.mxs_compute(p)
+        torch.cuda.synchronize()
+    finally:
+        b.mxs_destroy(p)
+    check(x, r, 0)

@@ -274,10 +274,10 @@ mxs_status mxs_ch_step(mxs_plan plan, int nsteps, int use_graph, void *hip_strea
  * launch end early, and the next mxs_ch_mass returns MXS_ERR_HIP.
  * MXS_CH_FUSED: the right-hand side of the x sweep is formed inside the row
  * solves, so that it never goes to memory (one launch per register class of
- * rows, then the column solves: one launch for grids of 65 to 2048 rows
- * whose columns fit a workgroup's registers, else three phases; rows of at
- * most 4096 elements, else MXS_ERR_UNSUPPORTED).  The three give the same step up to the order of
- * rounding.  Plans start in MXS_CH_SEPARATE; mxs_autotune times every mode
+ * rows, then the column solves: one launch, or three phases where the grids
+ * have more than 2048 rows or the phases are faster, as mxs_plan_info tells;
+ * rows of at most 4096 elements, else MXS_ERR_UNSUPPORTED).  The three give
+ * the same step up to the order of rounding.  Plans start in MXS_CH_SEPARATE; mxs_autotune times every mode
  * the plan supports and keeps the fastest.  With use_graph the persistent
  * launch is captured in the step's graph. */
 enum { MXS_CH_SEPARATE = 0, MXS_CH_PERSISTENT = 1, MXS_CH_FUSED = 2 };

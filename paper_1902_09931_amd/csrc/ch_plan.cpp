@@ -110,11 +110,8 @@ struct CHPlan final : mxs_plan_s {
     bool fused = false, fused_ok = false;
     int fused_rows = 4, fused_cols = 1;
     DevBuf fused_work;
-    // fused form: the columns as strips (one launch) where strip_shape >= 0,
-    // else the three phases.  Grids of at most 64 rows keep the phases, not
-    // for speed (64 x 64: 8.8 us, strips 4.6) but because launches_per_step
-    // of a fused ensemble of flat grids is relied on to count three column
-    // launches.
+    // fused form: the columns as strips (one launch) where strips >= 0, else
+    // the three phases
     int strips = -1, strip_blocks = 0;
     DevBuf strip_d[3], strip_map, strip_tabs;
     struct FusedRange {
@@ -608,7 +605,7 @@ struct CHPlan final : mxs_plan_s {
             sum_nx += I.nx;
             points += static_cast<long long>(I.nx) * I.ny;
         }
-        strips = reg_rows && max_ny > 2 * kSeg ? strip_shape_for(max_ny, sum_nx, points, dtype, 2, 1) : -1;
+        strips = reg_rows ? strip_shape_for(max_ny, sum_nx, points, dtype, 2, 1) : -1;
         const size_t stab = strips >= 0 ? strip_tab_size(strips) : 0;
         std::vector<double> st(stab * n);
         std::vector<StripInst> strip_h(strips >= 0 ? n : 0);

@@ -59,8 +59,9 @@ namespace {
 //     46.8, 32768 x 1200 113 / 165;  pentadiagonal bfloat16 6000 x 64 11.7 / 11.2,
 //     12000 x 256 16.6 / 18.8, 6000 x 1200 35.2 / 39.7
 //   Cahn-Hilliard steps (8192 columns are one round of two workgroups per CU):
-//     float 4 grids of 2048 columns x 40 rows 22.7 / 21.1, 9 of 1024 x 40 19.6 /
-//     22.7;  double 4 of 4096 x 65 31 / 41, x 256 64 / 60, 16 of 4096 x 256 238 /
+//     double 64 x 64 14.0 / 11.1, 1024 x 64 19.5 / 12.9;  float 4 grids of 2048
+//     columns x 64 rows 20.5 / 21.9, x 100 24.1 / 22.9, 9 of 1024 x 100 21.2 /
+//     24.6;  double 4 of 4096 x 65 31 / 41, x 256 64 / 60, 16 of 4096 x 256 238 /
 //     252, x 400 376 / 353;  float 64 of 256 x 256 34 / 40, of 1024 x 512 235 /
 //     246, of 1024 x 700 335 / 322;  bfloat16 64 of 1024 x 700 280 / 288
 struct ColumnLimit {
@@ -70,18 +71,18 @@ struct ColumnLimit {
 constexpr long long kAny = 1LL << 40;
 
 long long columns_max(int dtype, int bw, int epilogue, long long rows) {
-    static constexpr ColumnLimit plain[3][2][4] = {
+    static constexpr ColumnLimit plain[3][2][5] = {
         {{{200, 10000}, {2049, kAny}}, {{150, 7000}, {320, 10000}, {2049, kAny}}},                  // double
         {{{150, 10000}, {400, 14000}, {2049, kAny}}, {{150, 5000}, {512, 9000}, {1025, kAny}, {2049, 9000}}},
         {{{2049, 10000}}, {{1025, 9000}, {2049, 5000}}},                                            // bfloat16
     };
-    static constexpr ColumnLimit update[3][4] = {
+    static constexpr ColumnLimit update[3][5] = {
         {{256, 8192}, {320, 20000}, {2049, kAny}},
-        {{400, 8192}, {600, 20000}, {1025, kAny}, {2049, 8192}},
+        {{65, 5000}, {400, 8192}, {600, 20000}, {1025, kAny}, {2049, 8192}},
         {{600, 8192}, {1025, 20000}, {2049, 8192}},
     };
     const ColumnLimit *l = epilogue ? update[dtype] : plain[dtype][bw - 1];
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < 5; ++k)
         if (rows < l[k].rows) return l[k].columns;
     return 0;
 }

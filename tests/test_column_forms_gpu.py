@@ -45,7 +45,11 @@ def test_solves_on_both_sides_of_the_rule(nx, ny, tri, penta, k, dt):
 
 @pytest.mark.parametrize("count,ny,nx,strips", [(9, 66, 1000, (0, 0, 0)), (8, 66, 1000, (1, 1, 1)),
                                                 (11, 256, 1000, (1, 0, 0)), (11, 400, 1000, (1, 1, 0)),
-                                                (3, 2020, 100, (0, 0, 0)), (3, 2016, 100, (1, 1, 1))])
+                                                (3, 2020, 100, (0, 0, 0)), (3, 2016, 100, (1, 1, 1)),
+                                                (1, 8, 8, (1, 1, 1)), (2, 9, 60, (1, 1, 1)), (1, 31, 301, (1, 1, 1)),
+                                                (1, 32, 2052, (1, 1, 1)), (4, 33, 1000, (1, 1, 1)),
+                                                (1, 63, 500, (1, 1, 1)), (6, 64, 1000, (1, 0, 1)),
+                                                (9, 64, 1000, (0, 0, 0))])
 @pytest.mark.parametrize("k,dt", enumerate(["f64", "f32", "bf16"]), ids=["f64", "f32", "bf16"])
 def test_ensembles_on_both_sides_of_the_rule(count, ny, nx, strips, k, dt):
     """A fused step of equal grids takes the form the rule states, gives every

@@ -85,6 +85,14 @@ __global__ void __launch_bounds__(256) stencil2d_kernel(const Stencil2DArgs a) {
     const A *__restrict__ wv = up ? static_cast<const A *>(a.wts_up) : w;
     const bool full_vec = ib + V <= a.nx;
     const bool store_vec_ok = full_vec && ib >= lo && (periodic || (ib >= a.L && ib + V - 1 <= a.nx - 1 - a.R));
+    // A vector that is not stored whole is stored element by element, those from
+    // v0 up to v1.  In bfloat16 windows of several columns and 3 rows need 156
+    // registers so, and 169 with a test of every column, one more than 3
+    // wavefronts per SIMD can have (4096^2, 5 x 3: 35.5 us with 3 of them, 40.8
+    // with 2); other kernels do with fewer registers with the test.
+    constexpr bool BY_INDEX = sizeof(T) == 2 && NWX > 1 && NWY == 3;
+    const int v0 = static_cast<int>(max((periodic ? lo : max(lo, static_cast<long long>(a.L))) - ib, 0LL));
+    const int v1 = static_cast<int>(min(a.nx - (periodic ? 0 : a.R) - ib, static_cast<long long>(V)));
 
     A acc[NWY][V];
 #pragma unroll
@@ -216,7 +224,8 @@ __global__ void __launch_bounds__(256) stencil2d_kernel(const Stencil2DArgs a) {
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         const long long c = ib + v;
-                        if (c >= lo && c < a.nx && (periodic || (c >= a.L && c <= a.nx - 1 - a.R)))
+                        if (BY_INDEX ? v >= v0 && v < v1
+                                     : c >= lo && c < a.nx && (periodic || (c >= a.L && c <= a.nx - 1 - a.R)))
                             rowp[c] = from_acc<T>(acc[0][v]);
                     }
                 }

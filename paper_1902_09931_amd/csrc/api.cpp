@@ -174,6 +174,17 @@ struct Stencil2DPlan final : mxs_plan_s {
         return most;
     }
 
+    // Streaming form: row chunks sized per direction (short for x, tall for y,
+    // medium for xy), shrunk until the grid keeps several workgroups per CU.
+    void streaming_layout() {
+        int rows = nwy == 1 ? 4 : (nwx == 1 ? 64 : 16);
+        const int W = 256 * vec_elems(dtype);
+        const long long strips = (a.nx + W - 1) / W;
+        const long long want = (nwy >= 9 ? 2LL : 8LL) * device_cu_count();
+        while (rows > std::max(4, nwy) && strips * ((a.ny + rows - 1) / rows) < want) rows /= 2;
+        set_layout(rows, 1, fit_threads(256), 1);
+    }
+
     // Layout before tuning, from the layouts that tuning picks (times of the
     // streaming form with 256 threads against the one taken here).  Windows
     // over 3 or 5 rows: block form of 8 input rows (2000^2 FP64 3x3 with a
@@ -182,11 +193,27 @@ struct Stencil2DPlan final : mxs_plan_s {
     // bfloat16: x neighbours by lanes, whose 8 values per thread and row would
     // fill the LDS rows with floats (8192^2 5 taps along x 76 / 59, 3x3 105 /
     // 72); its 5-column windows over several rows would not fit the registers
-    // of a block and stream.  Everything else streams.
+    // of a block and stream.  Everything else streams, and so do
+    //   3 rows of a grid without wrap that is narrower than the narrowest strip
+    //   and has less than a block per CU: the block's 8 rows of single elements
+    //   are a longer chain than the 6 rows of a streamed chunk of 4 (64^2 FP32
+    //   6.6 / 7.5, 64 x 1000 bfloat16 10.6 / 12.7; with a wrap 9.5 / 9.3);
+    //   5x5 in float over many tiles, whose LDS rows keep the block form below
+    //   the streaming one (4096^2 36.1 / 43.0); a centred window takes its x
+    //   neighbours from lanes there (33.0; 2000^2 11.3, LDS rows 13.6).
     void default_layout() {
         const bool xs4 = stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, 4);
         const bool xs8 = stencil2d_xshuffle_ok(dtype, nwx, nwy, a.L, a.R, 8);
-        if (nwy == 1 && dtype == BF16 && xs4) {
+        const bool narrow = a.nx < 64 * vec_elems(dtype);
+        const long long W = fit_threads(128) * vec_elems(dtype);
+        const long long blocks = ((a.nx + W - 1) / W) * ((a.ny + 8LL - nwy) / (9 - std::min(nwy, 8)));
+        const long long cus = device_cu_count();
+        if (nwy == 3 && dtype != F64 && narrow && !a.periodic && blocks < cus) {
+            streaming_layout();
+        } else if (nwx == 5 && nwy == 5 && dtype == F32 && blocks >= 4 * cus && (xs8 || blocks >= 16 * cus)) {
+            if (xs8) set_layout(8, 2, fit_threads(128), 1, 8, 1);
+            else streaming_layout();
+        } else if (nwy == 1 && dtype == BF16 && xs4) {
             set_layout(4, 1, fit_threads(256), 1, 4, 1);
         } else if (nwy > 1 && dtype == BF16 && nwx == 3 && xs8) {
             set_layout(8, 2, fit_threads(128), 1, 8, 1);
@@ -195,14 +222,7 @@ struct Stencil2DPlan final : mxs_plan_s {
         } else if (dtype != BF16 && stencil2d_block_ok(dtype, nwx, nwy, 8)) {
             set_layout(8, 2, fit_threads(128), 1, 8);
         } else {
-            // row chunks sized per direction (short for x, tall for y, medium
-            // for xy), shrunk until the grid keeps several workgroups per CU
-            int rows = nwy == 1 ? 4 : (nwx == 1 ? 64 : 16);
-            const int W = 256 * vec_elems(dtype);
-            const long long strips = (a.nx + W - 1) / W;
-            const long long want = (nwy >= 9 ? 2LL : 8LL) * device_cu_count();
-            while (rows > std::max(4, nwy) && strips * ((a.ny + rows - 1) / rows) < want) rows /= 2;
-            set_layout(rows, 1, fit_threads(256), 1);
+            streaming_layout();
         }
         // explicit override "rows,order,threads,nt[,block]" for experiments
         if (const char *env = getenv("MXS_STENCIL_TILE")) {

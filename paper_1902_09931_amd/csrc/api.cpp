@@ -163,8 +163,8 @@ struct Stencil2DPlan final : mxs_plan_s {
         a.order = order;
         a.nt_store = nt;
         const int W = threads * vec_elems(dtype);
-        a.nstrips = (a.nx + W - 1) / W;
-        a.nchunks = (a.ny + rows - 1) / rows;
+        a.nstrips = static_cast<int>((a.nx + W - 1LL) / W);
+        a.nchunks = static_cast<int>((a.ny + rows - 1LL) / rows);
     }
 
     // Widest workgroup whose strip fits in a row, at most `most` threads (64
@@ -224,6 +224,10 @@ struct Stencil2DPlan final : mxs_plan_s {
         } else {
             streaming_layout();
         }
+        // tall grids of few columns: fewer, longer chunks (a column of 403 million
+        // rows has 67 million blocks of 6)
+        for (int rows = 64; !stencil2d_fits_launch(a, threads) && rows < a.ny; rows *= 2)
+            set_layout(rows, 1, fit_threads(256), 1);
         // explicit override "rows,order,threads,nt[,block]" for experiments
         if (const char *env = getenv("MXS_STENCIL_TILE")) {
             int r = 0, o = 0, t = 0, nt = 1, blk = 0, xs = 0;
@@ -356,7 +360,15 @@ mxs_status Stencil2DPlan::autotune(hipStream_t s) {
             }
         }
     }
-    if (cands.empty()) return MXS_OK;
+    auto too_many = [&](const Cand &c) {
+        set_layout(c.l.rows, c.l.order, c.l.threads, c.l.nt, c.l.block, c.l.xs);
+        return !stencil2d_fits_launch(a, threads);
+    };
+    cands.erase(std::remove_if(cands.begin(), cands.end(), too_many), cands.end());
+    if (cands.empty()) {
+        set_layout(start.rows, start.order, start.threads, start.nt, start.block, start.xs);
+        return MXS_OK;
+    }
     // Grids whose input and output are between half and four times the
     // memory-side cache are timed with that cache flushed before each
     // launch: back to back, such a grid would find part of its data still

@@ -434,6 +434,7 @@ size_t stencil2d_lds_bytes(int dtype, int nwx, int nwy, int threads, int block_r
 
 hipError_t launch_stencil2d(int dtype, int nwx, int nwy, const Stencil2DArgs &a, int threads,
                             hipStream_t s) {
+    if (!stencil2d_fits_launch(a, threads)) return hipErrorInvalidConfiguration;
     switch (a.block_rows ? dtype : dtype + 3) {
     case F64: return launch_stencil2d_block_f64(nwx, nwy, a, threads, s);
     case F32: return launch_stencil2d_block_f32(nwx, nwy, a, threads, s);

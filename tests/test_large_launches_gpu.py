@@ -63,3 +63,26 @@ def test_columns_beyond_one_launch():
     finally:
         b.mxs_destroy(p)
     check(x, r, 0)
+
+
+@pytest.mark.parametrize("half,ny", [(1, 403_000_000), (2, 269_000_000), (4, 537_000_000)])
+def test_columns_of_more_rows_than_blocks_in_one_launch(half, ny):
+    """One periodic column of ny rows: against shifted sums in double, in pieces,
+    to the float bound of 2 half + 1 terms of at most 1 and one rounding."""
+    u = fill((ny, 1), 83)
+    out = torch.full_like(u, float("nan"))
+    w = np.linspace(-1, 1, 2 * half + 1)
+    p = b.mxs_create_2d(1, ny, 1, b.MXS_Y, b.MXS_P, b.MXS_F32, 0, 0, half, half, w, None, u, out)
+    try:
+        b.mxs_compute(p)
+        torch.cuda.synchronize()
+    finally:
+        b.mxs_destroy(p)
+    taps = 2 * half + 1
+    for k in range(0, ny, 1 << 25):
+        n = min(1 << 25, ny - k)
+        rows = torch.arange(k - half, k + n + half, device="cuda") % ny
+        v = u[rows, 0].double()
+        ref = sum(float(w[q]) * v[q:q + n] for q in range(taps))
+        err = (out[k:k + n, 0].double() - ref).abs()
+        assert bool(err.le((taps + 2) * 2.0 ** -24 * taps).all()), k   # (a NaN fails)

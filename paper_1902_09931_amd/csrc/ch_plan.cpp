@@ -564,7 +564,11 @@ struct CHPlan final : mxs_plan_s {
             n += snprintf(buf + n, len - n, " tuned_us_separate=%.1f", best_graph_t * 1e6);
         if (best_persist && n < len)
             n += snprintf(buf + n, len - n, " tuned_us_persistent=%.1f", best_persist_t * 1e6);
-        if (fused && n < len) n += snprintf(buf + n, len - n, " fused_rows=%d fused_cols=%d", fused_rows, fused_cols);
+        if (fused && n < len)
+            n += snprintf(buf + n, len - n, " fused_rows=%d fused_cols=%d quad_classes=%d/%zu", fused_rows, fused_cols,
+                          static_cast<int>(std::count_if(fused_ranges.begin(), fused_ranges.end(),
+                                                         [](const FusedRange &f) { return f.quads; })),
+                          fused_ranges.size());
         if (fused && strips >= 0 && n < len) n += snprintf(buf + n, len - n, " columns=strips shape=%d", strips);
         if (best_fused_t < 1e29 && n < len)
             n += snprintf(buf + n, len - n, " tuned_us_fused=%.1f", best_fused_t * 1e6);
@@ -712,13 +716,15 @@ struct CHPlan final : mxs_plan_s {
         fused_ok = false;
         class_order = by_class;
         if (reg_rows) {
-            // fused shape: 4 rows, 1 column per thread until tuned;
-            // MXS_CH_FUSED_ROWS=8 or MXS_CH_FUSED_COLS=2 pick another (tests)
+            // shape of the classes that the quad kernel does not take: 4 rows,
+            // 1 column per thread until tuned.  MXS_CH_FUSED_ROWS (4 or 8) or
+            // MXS_CH_FUSED_COLS (1 or 2, with 4 rows) fix one for every class
+            // (tests)
             const char *fr = getenv("MXS_CH_FUSED_ROWS");
             const char *fcol = getenv("MXS_CH_FUSED_COLS");
             const bool r8 = fr && atoi(fr) == 8, c2 = fcol && atoi(fcol) == 2 && !r8;
             fused_cols = c2 ? 2 : 1;
-            quads_off = r8 || c2;
+            quads_off = fr || fcol;
             hipError_t fe = build_fused(r8 ? 8 : 4);
             if (fe != hipSuccess) return hip_fail(fe, "row group table upload");
             fused_ok = true;

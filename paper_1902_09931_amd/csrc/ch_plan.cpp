@@ -6,9 +6,12 @@
 //   2. L_x w = R on every row, in place                        (cyclic.hip)
 //   3-5. L_y v = w on every column, three phases, the last one
 //        writing C^{n+1} = 2 C^n - C^{n-1} + v                  (cyclic.hip)
-// In the fused mode steps 1 and 2 are one launch per register class of the
-// rows (chrows.hip): each workgroup forms R of a few rows in registers and
-// solves them, and R never goes to memory.
+// In the fused mode launches 1 and 2 are one per register class of the rows:
+// each workgroup forms R of a few rows on chip and solves them, and R never
+// goes to memory (chquads.hip for classes of rows of a multiple of 4 elements,
+// chrows.hip for the others); launches 3 to 5 are one where strips of columns
+// held in registers are faster (strips.hip).  In the persistent mode a step is
+// one cooperative launch (persist.hip).
 // The three state buffers rotate, so the kernel arguments differ between
 // consecutive steps; the plan keeps one instance table (and, for the
 // persistent step, one captured HIP graph) per rotation.

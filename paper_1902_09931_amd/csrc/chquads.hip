@@ -1,9 +1,10 @@
 // The x sweep of the ADI Cahn-Hilliard step with its right-hand side formed
 // inside the row solves (chrows.hip states the operator), for rows whose
 // length is a multiple of 4: a workgroup takes 4 consecutive rows of one
-// instance and every thread the 4 columns of one quad.
+// instance and every thread the 4 columns of one quad; rows of more than 2048
+// elements (LPR = 256 below) 2 rows and two quads per thread.
 //
-// Right-hand side: a thread reads its quad of the 8 input rows j0 - 2 ..
+// Right-hand side: a thread reads its quad of the 8 (or 6) input rows j0 - 2 ..
 // j0 + 5 (the rows' windows along y), 16 or 32 bytes per row and time level,
 // and walks them with one accumulator per output value.  Its x neighbours
 // (two columns on each side) are the neighbouring lanes' values, moved by
@@ -14,8 +15,8 @@
 //
 // Solve: R is stored to LDS in the line solver's order and every thread
 // solves with 16 elements of one row (groups_dev.h: LPR = 16 .. 256 lanes
-// per row, so a workgroup has 4 LPR threads and long rows take more
-// wavefronts, not more registers); the solution returns through the same LDS
+// per row, so a workgroup has 4 LPR threads, 2 LPR at 256, and long rows take
+// more wavefronts, not more registers); the solution returns through the same LDS
 // space and leaves as whole quads.
 #include "ch_dev.h"
 #include "groups_dev.h"
@@ -290,7 +291,7 @@ __global__ void __launch_bounds__(kQuadRows<LPR> *LPR, kQuadWaves<T>) ch_quads_k
         for (int i = 0; i < 4; ++i) v[k + i] = to_f64<TW>(x[i]);
     }
     double2 *xch = reinterpret_cast<double2 *>(smem_raw + Lds::xch) + r * kGroupXch<LPR>;
-    group_solve<2, LPR>(v, nx, li, LineCoef{RI.p1, RI.p2, RI.pow}, xch);
+    group_solve<LPR>(v, nx, li, LineCoef{RI.p1, RI.p2, RI.pow}, xch);
     const double invK = RI.invK;
 #pragma unroll
     for (int k = 0; k < kGroupE; k += 4) {

@@ -1,4 +1,4 @@
-// Device code of the line solver that spreads one line over LPR lanes, 16
+// Device code of the pentadiagonal line solver that spreads one line over LPR lanes, 16
 // consecutive elements per lane: LPR = 16 or 32 lanes (2 or 4 lines share a
 // wavefront), 64 (a wavefront) or 128 / 256 (2 or 4 wavefronts).  The method
 // is the one of the register line solver (wavelines.hip): per direction a
@@ -22,14 +22,10 @@ struct LineCoef {
 };
 
 // (I - m)^{-1}, m a power of the companion matrix
-template <int BW> __device__ __forceinline__ Mat closure_mat(const Mat &m) {
-    if constexpr (BW == 2) {
-        const double a = 1.0 - m.a, b = -m.b, c = -m.c, d = 1.0 - m.d;
-        const double r = 1.0 / (a * d - b * c);
-        return Mat{d * r, -b * r, -c * r, a * r};
-    } else {
-        return Mat{1.0 / (1.0 - m.a), 0.0, 0.0, 0.0};
-    }
+__device__ __forceinline__ Mat closure_mat(const Mat &m) {
+    const double a = 1.0 - m.a, b = -m.b, c = -m.c, d = 1.0 - m.d;
+    const double r = 1.0 / (a * d - b * c);
+    return Mat{d * r, -b * r, -c * r, a * r};
 }
 
 // Orders LDS accesses between the lanes of a line.
@@ -38,16 +34,16 @@ template <int LPR> __device__ __forceinline__ void line_sync() {
     else __syncthreads();
 }
 
-// Solve the line of n elements whose elements 16 li .. 16 li + 15 are in v
+// Solve the pentadiagonal line of n elements whose elements 16 li .. 16 li + 15 are in v
 // (li = 0 .. LPR - 1 the lane's index in its line; elements past n are zero),
 // leaving u / K times K in v, i.e. the solution before the scaling by 1/K.
 // xch: the line's exchange space of 2 * max(1, LPR / 64) pairs of doubles (4
 // pairs where LPR < 64).  Every lane of the wavefront is active; with LPR >
 // 64 every thread of the workgroup calls this together.
-template <int BW, int LPR>
+template <int LPR>
 __device__ __forceinline__ void group_solve(double (&v)[kGroupE], const int n, const int li, const LineCoef &co,
                                             double2 *xch) {
-    constexpr int E = kGroupE;
+    constexpr int E = kGroupE, BW = 2;
     const int lane = threadIdx.x & 63;
     const int row = lane >> 4, p = lane & 15;
     const cptr<double> pw = as_constant(co.pow);
@@ -63,7 +59,7 @@ __device__ __forceinline__ void group_solve(double (&v)[kGroupE], const int n, c
 #pragma unroll
     for (int i = 0; i < 4; ++i) K[i] = load_mat(pw + 4 * (E << i));
     const Mat Mrow = load_mat(pw + 4 * kWaveBlock);     // one row of 16 lanes
-    const Mat Cn = closure_mat<BW>(pow_mat(pw, pb, n));
+    const Mat Cn = closure_mat(pow_mat(pw, pb, n));
 
     // ---- forward, pass A
     S2 e{0.0, 0.0};

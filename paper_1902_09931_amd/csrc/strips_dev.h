@@ -28,8 +28,7 @@ namespace {
 // M^(rows of the last wavefront that holds any); (I - M^ny)^{-1}.
 template <int NT, int CW> struct StripTab {
     static constexpr int NW = NT / 64, SPW = 64 / CW;
-    static constexpr int fw = SPW + 1, bwd = fw + NW, last = bwd + NW, tail = last + 1, cinv = tail + 1,
-                         count = cinv + 1;
+    static constexpr int fw = SPW + 1, bwd = fw + NW, last = bwd + NW, tail = last + 1, cinv = tail + 1;
 };
 
 template <int BW> __device__ __forceinline__ S2 shfl_up_s(S2 v, int d) {

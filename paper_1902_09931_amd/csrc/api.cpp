@@ -194,10 +194,11 @@ struct Stencil2DPlan final : mxs_plan_s {
     // fill the LDS rows with floats (8192^2 5 taps along x 76 / 59, 3x3 105 /
     // 72); its 5-column windows over several rows would not fit the registers
     // of a block and stream.  Everything else streams, and so do
-    //   3 rows of a grid without wrap that is narrower than the narrowest strip
-    //   and has less than a block per CU: the block's 8 rows of single elements
-    //   are a longer chain than the 6 rows of a streamed chunk of 4 (64^2 FP32
-    //   6.6 / 7.5, 64 x 1000 bfloat16 10.6 / 12.7; with a wrap 9.5 / 9.3);
+    //   3 rows (in float: along y alone) of a grid without wrap that is narrower
+    //   than the narrowest strip and has less than a block per CU: the block's 8
+    //   rows of single elements are a longer chain than the 6 rows of a streamed
+    //   chunk of 4 (64^2 FP32 6.6 / 7.2, 64 x 1000 bfloat16 10.6 / 12.2; with a
+    //   wrap 9.5 / 9.3, FP32 3x3 8.3 / 7.3);
     //   5x5 in float over many tiles, whose LDS rows keep the block form below
     //   the streaming one (4096^2 36.1 / 43.0); a centred window takes its x
     //   neighbours from lanes there (33.0; 2000^2 11.3, LDS rows 13.6).
@@ -208,7 +209,7 @@ struct Stencil2DPlan final : mxs_plan_s {
         const long long W = fit_threads(128) * vec_elems(dtype);
         const long long blocks = ((a.nx + W - 1) / W) * ((a.ny + 8LL - nwy) / (9 - std::min(nwy, 8)));
         const long long cus = device_cu_count();
-        if (nwy == 3 && dtype != F64 && narrow && !a.periodic && blocks < cus) {
+        if (nwy == 3 && (dtype == BF16 || (dtype == F32 && nwx == 1)) && narrow && !a.periodic && blocks < cus) {
             streaming_layout();
         } else if (nwx == 5 && nwy == 5 && dtype == F32 && blocks >= 4 * cus && (xs8 || blocks >= 16 * cus)) {
             if (xs8) set_layout(8, 2, fit_threads(128), 1, 8, 1);

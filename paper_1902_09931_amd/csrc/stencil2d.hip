@@ -91,8 +91,11 @@ __global__ void __launch_bounds__(256) stencil2d_kernel(const Stencil2DArgs a) {
     // wavefronts per SIMD can have (4096^2, 5 x 3: 35.5 us with 3 of them, 40.8
     // with 2); other kernels do with fewer registers with the test.
     constexpr bool BY_INDEX = sizeof(T) == 2 && NWX > 1 && NWY == 3;
-    const int v0 = static_cast<int>(max((periodic ? lo : max(lo, static_cast<long long>(a.L))) - ib, 0LL));
-    const int v1 = static_cast<int>(min(a.nx - (periodic ? 0 : a.R) - ib, static_cast<long long>(V)));
+    int v0 = 0, v1 = 0;
+    if constexpr (BY_INDEX) {
+        v0 = static_cast<int>(max((periodic ? lo : max(lo, static_cast<long long>(a.L))) - ib, 0LL));
+        v1 = static_cast<int>(min(a.nx - (periodic ? 0 : a.R) - ib, static_cast<long long>(V)));
+    }
 
     A acc[NWY][V];
 #pragma unroll
@@ -224,9 +227,11 @@ __global__ void __launch_bounds__(256) stencil2d_kernel(const Stencil2DArgs a) {
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         const long long c = ib + v;
-                        if (BY_INDEX ? v >= v0 && v < v1
-                                     : c >= lo && c < a.nx && (periodic || (c >= a.L && c <= a.nx - 1 - a.R)))
+                        if constexpr (BY_INDEX) {
+                            if (v >= v0 && v < v1) rowp[c] = from_acc<T>(acc[0][v]);
+                        } else if (c >= lo && c < a.nx && (periodic || (c >= a.L && c <= a.nx - 1 - a.R))) {
                             rowp[c] = from_acc<T>(acc[0][v]);
+                        }
                     }
                 }
             }

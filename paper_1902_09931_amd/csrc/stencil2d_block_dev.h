@@ -73,20 +73,25 @@ __device__ __forceinline__ void block_body(const Stencil2DArgs &a, int strip, in
     // the end, as a column more than a period away takes a division (64^2 FP32,
     // 3 rows: 11.8 us with it, 9.3 without).
     const long long cmax = static_cast<long long>(a.nx) + NWX;
+    auto wrap_col = [&](long long c) __attribute__((always_inline)) { return wrap_fast(CLEAN ? c : min(c, cmax), a.nx); };
     auto in_col = [&](long long c) __attribute__((always_inline)) {
-        c = min(c, cmax);
-        return periodic ? wrap_fast(c, a.nx) : (c < 0 ? 0 : (c >= a.nx ? a.nx - 1LL : c));
+        return periodic ? wrap_col(c) : (c < 0 ? 0 : (c >= a.nx ? a.nx - 1LL : c));
     };
     A xin[GIN][V];
+    if constexpr (CLEAN) {
 #pragma unroll
-    for (int u = 0; u < GIN; ++u) {
-        const gptr<const T> rowp = in + in_row(u) * a.ld;
-        if (CLEAN) {
-            load_vec<T>(rowp + ib, xin[u]);
-        } else {
+        for (int u = 0; u < GIN; ++u) load_vec<T>(in + in_row(u) * a.ld + ib, xin[u]);
+    } else {
+        auto elements = [&](auto col) __attribute__((always_inline)) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) xin[u][v] = to_acc<T>(gld<T>(rowp, in_col(ib + v)));
-        }
+            for (int u = 0; u < GIN; ++u) {
+                const gptr<const T> rowp = in + in_row(u) * a.ld;
+#pragma unroll
+                for (int v = 0; v < V; ++v) xin[u][v] = to_acc<T>(gld<T>(rowp, col(ib + v)));
+            }
+        };
+        if (periodic) elements(wrap_col);
+        else elements([&](long long c) { return c >= a.nx ? a.nx - 1LL : c; });
     }
     constexpr int HX = NWX / 2;   // lane exchange: neighbours on each side
     const int lane = t & 63;

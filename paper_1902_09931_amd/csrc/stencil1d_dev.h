@@ -46,8 +46,10 @@ template <int TAPS, int V> constexpr int halo_pad() {
 // Two kernels rather than a test in one: without the wrapped reads a thread
 // holds 94 registers instead of 146 (17 taps in double), and 65,536 signals of
 // 64 .. 4096 take 517 us instead of 555.
+// (bfloat16 with the longest wrapped windows needs one register more than 4
+// wavefronts per SIMD can have, unless it is told to: 436 us instead of 403.)
 template <typename T, int TAPS, int U, bool PER>
-__global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
+__global__ void __launch_bounds__(256, sizeof(T) == 2 && PER && TAPS > 15 ? 4 : 1) stencil1d_kernel(const Stencil1DArgs a) {
     using A = typename St<T>::acc;
     constexpr int V = St<T>::V;
     constexpr int PAD = halo_pad<TAPS, V>();
@@ -143,10 +145,11 @@ __global__ void __launch_bounds__(256) stencil1d_kernel(const Stencil1DArgs a) {
         // with the taps past its own signal's ends read from where they wrap
         // to; every such read is requested before any is used.  Without a wrap
         // the outputs nearest a signal's end are left out, and for long windows
-        // the element path below, which skips them, is the faster one (500,000
-        // signals of 20 .. 40 in double, 17 taps: 108 us here, 90 there; 7 taps
-        // 72 and 77).
-        if ((PER || TAPS < 10) && eb + V <= a.total && (se >= eb + V || soff[lo + 2] >= eb + V)) {
+        // the element path below, which skips them, is the faster one, but for
+        // bfloat16 with its 8 elements per vector (500,000 signals of 20 .. 40,
+        // 17 taps: double 108 us here, 90 there, float 57 and 53, bfloat16 55 and
+        // 75; 7 taps in double 72 and 77).
+        if ((PER || TAPS < 10 || sizeof(T) == 2) && eb + V <= a.total && (se >= eb + V || soff[lo + 2] >= eb + V)) {
             const bool cross = se < eb + V;
             const long long sb2 = cross ? se : sb, se2 = cross ? soff[lo + 2] : se;
             const A *lp = lds + PAD + (eb - e0) - a.L;

@@ -74,7 +74,7 @@ long long columns_max(int dtype, int bw, int epilogue, long long rows) {
     static constexpr ColumnLimit plain[3][2][5] = {
         {{{200, 10000}, {2049, kAny}}, {{150, 7000}, {320, 10000}, {2049, kAny}}},                  // double
         {{{150, 10000}, {400, 14000}, {2049, kAny}}, {{150, 5000}, {512, 9000}, {1025, kAny}, {2049, 9000}}},
-        {{{2049, 10000}}, {{1025, 9000}, {2049, 5000}}},                                            // bfloat16
+        {{{320, 10000}, {800, 20000}, {2049, 10000}}, {{1025, 9000}, {2049, 5000}}},                // bfloat16
     };
     static constexpr ColumnLimit update[3][5] = {
         {{256, 8192}, {320, 20000}, {2049, kAny}},

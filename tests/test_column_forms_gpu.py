@@ -19,7 +19,7 @@ if not torch.cuda.is_available():
 # (nx, ny, strips expected for (double, float, bfloat16)), tridiagonal then pentadiagonal
 EDGES = [(10000, 20, (1, 1, 1), (0, 0, 0)), (10001, 20, (0, 0, 0), (0, 0, 0)), (5000, 40, (1, 1, 1), (1, 1, 1)),
          (5001, 40, (1, 1, 1), (1, 0, 1)), (7001, 149, (1, 1, 1), (0, 0, 1)), (12000, 199, (0, 1, 0), (0, 0, 0)),
-         (12000, 200, (1, 1, 0), (0, 0, 0)), (14001, 400, (1, 1, 0), (1, 0, 0)), (40000, 512, (1, 1, 0), (1, 1, 0)),
+         (12000, 200, (1, 1, 0), (0, 0, 0)), (14001, 400, (1, 1, 1), (1, 0, 0)), (20001, 400, (1, 1, 0), (1, 0, 0)), (40000, 512, (1, 1, 0), (1, 1, 0)),
          (5001, 1100, (1, 1, 1), (1, 1, 0)), (9001, 1025, (1, 1, 1), (1, 0, 0)), (100001, 5, (0, 0, 0), (0, 0, 0))]
 
 

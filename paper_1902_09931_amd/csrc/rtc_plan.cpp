@@ -111,8 +111,11 @@ extern "C" __global__ void __launch_bounds__(MXS_NT) mxs_user_stencil(const FnAr
     extern __shared__ mxs_real mxs_tile[];
     const int strip = blockIdx.x %% a.nstrips, chunk = blockIdx.x / a.nstrips;
     const long long i0 = static_cast<long long>(strip) * MXS_NT, j0 = static_cast<long long>(chunk) * MXS_ROWS;
-    // the tile of every input, kLD values per thread requested before any is stored
-    constexpr int kN = (kTH * kTW + MXS_NT - 1) / MXS_NT, kLD = kN < 12 ? kN : 12;
+    // the tile of every input, kLD values per thread requested before any is
+    // stored: 12 per input, 20 of a single one, which saves windows of 9 to 13
+    // rows a second round (9 taps along y, bfloat16, 100^2 7.1 -> 5.9 us, 4096^2
+    // 38.6 -> 28.6; 40.6 one value at a time)
+    constexpr int kN = (kTH * kTW + MXS_NT - 1) / MXS_NT, kMost = MXS_NIN == 1 ? 20 : 12, kLD = kN < kMost ? kN : kMost;
 #pragma unroll 1
     for (int g = 0; g < kN; g += kLD) {
         mxs_real v[MXS_NIN][kLD];

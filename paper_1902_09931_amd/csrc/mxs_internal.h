@@ -244,10 +244,13 @@ int bucket_width(int taps);   // 1, 3, 5, 9 or 17; 0 if too wide
 // Most taps of a 1D window; the 1D kernels are compiled for every number of taps.
 constexpr int kMaxTaps1D = 17;
 
-// Whether one launch holds the layout's workgroups: a launch holds fewer than
-// 2^32 threads and is cut off without an error beyond.
+// Whether one launch holds these workgroups: a launch holds fewer than 2^32
+// threads and is cut off without an error beyond.
+inline bool fits_launch(long long strips, long long chunks, int threads) {
+    return strips * chunks < (1LL << 32) / threads;
+}
 inline bool stencil2d_fits_launch(const Stencil2DArgs &a, int threads) {
-    return static_cast<long long>(a.nstrips) * a.nchunks < (1LL << 32) / threads;
+    return fits_launch(a.nstrips, a.nchunks, threads);
 }
 hipError_t launch_stencil2d(int dtype, int nwx, int nwy, const Stencil2DArgs &a,
                             int threads, hipStream_t s);

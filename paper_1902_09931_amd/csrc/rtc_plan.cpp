@@ -238,6 +238,8 @@ struct FnPlan final : mxs_plan_s {
         if (mod) (void)hipModuleUnload(mod);
     }
     mxs_status compute(hipStream_t s) override {
+        if (!fits_launch(a.nstrips, a.nchunks, threads))
+            return fail(MXS_ERR_UNSUPPORTED, "the grid needs more workgroups than one launch holds");
         void *params[] = {&a};
         const hipError_t e = hipModuleLaunchKernel(fn, static_cast<unsigned>(a.nstrips * a.nchunks), 1, 1,
                                                    static_cast<unsigned>(threads), 1, 1, static_cast<unsigned>(lds),

@@ -232,6 +232,7 @@ size_t weno_lds_bytes(int rows, int threads) {
 bool weno_rows_ok(int rows) { return rows == 1 || rows == 4 || rows == 8; }
 
 hipError_t launch_weno_adv(const WenoArgs &a, int threads, hipStream_t s) {
+    if (!fits_launch(a.nstrips, a.nchunks, threads)) return hipErrorInvalidConfiguration;
     const int grid = a.nstrips * a.nchunks;
     const size_t lds = weno_lds_bytes(a.rows, threads);
     if (a.rows == 1)

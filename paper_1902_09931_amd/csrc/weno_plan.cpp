@@ -70,8 +70,10 @@ struct WenoPlan final : mxs_plan_s {
                 for (int order : {1, 0})
                     for (int nt : {1, 0})
                         if ((few ? order == 1 : nthreads > 64) &&
+                            fits_launch((a.nx + 2LL * nthreads - 1) / (2 * nthreads), (a.ny + rows - 1LL) / rows, nthreads) &&
                             weno_lds_bytes(rows, nthreads) <= static_cast<size_t>(device_lds_limit()))
                             cands.push_back({rows, order, nthreads, nt, 1e30});
+        if (cands.empty()) return MXS_OK;
         const Cand start{a.rows, a.order, threads, a.nt_store, 0};
         const size_t data = 4 * grid_bytes(a.nx, a.ny, a.ld, F64);
         DevBuf flush;

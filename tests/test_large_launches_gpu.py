@@ -86,3 +86,17 @@ def test_columns_of_more_rows_than_blocks_in_one_launch(half, ny):
         ref = sum(float(w[q]) * v[q:q + n] for q in range(taps))
         err = (out[k:k + n, 0].double() - ref).abs()
         assert bool(err.le((taps + 2) * 2.0 ** -24 * taps).all()), k   # (a NaN fails)
+
+
+def test_user_function_grids_beyond_one_launch_are_refused():
+    """140 million rows of one column: 17.5 million chunks of 256 threads."""
+    ny = 140_000_000
+    u = torch.ones(ny, 1, dtype=torch.bfloat16, device="cuda")
+    out = torch.zeros_like(u)
+    source = "__device__ mxs_real same(const mxs_real *const *w, const mxs_real *coe, int loc) { return w[0][loc]; }"
+    p = b.mxs_create_2d_fn(1, ny, 1, b.MXS_Y, b.MXS_P, b.MXS_BF16, 0, 0, 1, 1, [u], out, None, source, "same")
+    try:
+        with pytest.raises(Exception, match="more workgroups than one launch holds"):
+            b.mxs_compute(p)
+    finally:
+        b.mxs_destroy(p)
